@@ -1,0 +1,539 @@
+// dps_gemm256.hip -- the 256 x 256 tile of the nested linear (gfx950): prefill
+// on FP16 activations (full and fast mode) and on FP8 activations.
+//
+// Full mode merges the upper and residual bytes into FP16 operands in
+// registers (Sec. IV-C: reconstruction during computation), fast mode
+// converts the upper bytes alone, both for v_mfma_f32_16x16x32_f16; the FP8
+// kind feeds the upper bytes as stored (E5M2, or E4M3 whose fast-mode value is
+// E4M3 * 2^-8) to v_mfma_f32_16x16x128_f8f6f4 against E4M3 activations and
+// applies the row scale to the fp32 sums.
+//
+// Bound: matrix work, 2048 MFMA cycles per SIMD and stage in every kind, and
+// under sustained load the card's power (a plain library FP16 GEMM of these
+// shapes reaches 1.45 PFLOP/s on random data and 2.1 on zeros).  One block of
+// eight waves (4 x 2, wave tile 64 weight rows x 128 tokens) fills a CU:
+// 128 fp32 accumulators per lane and 160 KiB of LDS.  What the split and the
+// loop are built for:
+//   - 256 x 256 reads the fewest LDS bytes per flop that fit: a stage (64 K
+//     elements, FP8 128) is 32 KiB of tokens and 32 KiB of weights (fast mode
+//     16), each wave reads 24 KiB of fragments for 64 MFMAs;
+//   - software pipeline over the one barrier per stage: it stands before the
+//     last two of a stage's eight token tiles, when every fragment of the
+//     stage is in registers, so its slots can be refilled at once and the next
+//     stage's first reads run beside the remaining MFMAs.  The weight operands
+//     of the next stage are merged between the MFMAs of the last and the
+//     first token tile;
+//   - the steady state issues direct-to-LDS loads with almost no address
+//     arithmetic: buffer loads with a scalar stage offset, or (full mode,
+//     whose two planes share a line) one 64-bit add per load from pointers
+//     that are renewed only where a lane leaves its residual chunk;
+//   - output stores without per-element checks when the tile is whole.
+// MI355X, against the earlier kernels on these tiles (barrier at the head of
+// a stage, all reads and merges behind it): gate+up 28672 x 4096 in full mode
+// 1871 -> 1655 us at 8192 tokens and 408 -> 352 at 1531, fast mode 1578 ->
+// 1455, FP8 with its quantization 972 -> 820; down 4096 x 14336 in full mode
+// at 8192 tokens 917 -> 796.  Moving the loads elsewhere in the stage (all at
+// the barrier, one per token tile, alternating between the two waves of a
+// SIMD, one wave at a time) changed the time by -2 to +30%: each costs its
+// wave 60-115 cycles wherever it stands, about 0.3 of the 1.6 us a stage
+// takes at full clock.
+#include "dps_gemm_common.h"
+
+namespace dps {
+
+namespace {
+
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void store_half4(uint16_t *p, f32x4 v)
+{
+    *reinterpret_cast<half4 *>(p) = half4{(_Float16)v.x, (_Float16)v.y, (_Float16)v.z,
+                                          (_Float16)v.w};
+}
+
+enum { T_FULL = 0, T_FAST = 1, T_FP8 = 2 };
+
+// Rings of WS weight and XS token stages.
+template <int KIND>
+struct T256 {
+    static constexpr int BK = KIND == T_FP8 ? 128 : 64;   // K elements per stage
+    static constexpr int W_SLOT = (KIND == T_FAST ? 16 : 32) * 1024;
+    static constexpr int X_SLOT = 32 * 1024;
+    static constexpr int WS = KIND == T_FAST ? 4 : 3;
+    static constexpr int XS = KIND == T_FAST ? 3 : 2;
+    static constexpr int X_BASE = W_SLOT * WS;
+    static constexpr int LDS = X_BASE + X_SLOT * XS;
+    static constexpr int NW = W_SLOT / 1024 / 8;  // DMA instructions per wave per stage
+    static constexpr int NX = X_SLOT / 1024 / 8;
+    static constexpr int XB = KIND == T_FP8 ? 1 : 2;  // bytes per activation
+    static constexpr int RAW = KIND == T_FAST ? 4 : 8;
+    // group u of a wave's DMA is tokens of stage u + XS, then weights of
+    // stage u + WS; at the barrier of stage t (groups up to t - 1 are out)
+    // these may still be in flight without touching stage t + 1
+    static constexpr int OUTSTANDING = (XS < WS ? NW : 0) + (XS - 2) * (NX + NW);
+    static_assert(XS >= 2 && WS >= XS && LDS <= 160 * 1024, "rings");
+};
+
+// LDS lines of 128 bytes, 16-byte chunks at slot chunk ^ swz8(line).
+// Weights: full mode line r holds row r, its 64 upper bytes in chunks 0-3 and
+// its 64 residual bytes in chunks 4-7; fast mode line 16 t + i holds row
+// 32 t + i in chunks 0-3 and row 32 t + 16 + i in chunks 4-7; FP8 line r holds
+// 128 upper bytes of row r.  A fragment read of lane (i, g) is chunk 4q + g of
+// 16 lines, conflict-free.
+// Tokens: FP8 as the weights.  FP16 K chunk c (8 elements) of a row sits at
+// slot sigma(c) ^ swz8(row), sigma(c) = (c >> 1) | (c & 1) << 2, so that the
+// chunks 2g + q which lane group g reads in MFMA step q are four consecutive
+// slots too (plain order costs bank conflicts, half of the LDS cycles);
+// tok_chunk is sigma's inverse, the chunk the DMA writes into a slot.
+// Either way both operands of an MFMA pair the same K elements.
+__device__ __forceinline__ int tok_chunk(int slot) { return ((slot & 3) << 1) | (slot >> 2); }
+
+// A raw buffer over [p, p + bytes): 48-bit base, byte count, data format 32
+// (the descriptor of untyped buffers on gfx9).  Loads past the end return zero.
+typedef int32_t rsrc_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void *p, int64_t bytes)
+{
+    const uint64_t b = (uint64_t)p;
+    return rsrc_t{__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
+                  __builtin_amdgcn_readfirstlane((int)((b >> 32) & 0xFFFFu)),
+                  __builtin_amdgcn_readfirstlane((int)(bytes < 0xFFFFFFFFll ? bytes : 0xFFFFFFFFll)),
+                  0x00020000};
+}
+
+// buffer_load_dwordx4 ... lds: 16 bytes per lane from buffer offset voffset +
+// soffset into the wave's 1 KiB at `lds`.
+__device__ void buffer_load_lds(rsrc_t rsrc, __attribute__((address_space(3))) void *lds, int size,
+                                int voffset, int soffset, int offset,
+                                int aux) __asm("llvm.amdgcn.raw.buffer.load.lds");
+
+// The value, opaque to the optimizer: what the rare paths of the stage loop
+// derive from it is computed there instead of being kept in registers.
+__device__ __forceinline__ int unhoisted(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// lgkmcnt(0).  Scalar loads retire out of order with LDS reads, and a rare
+// path of the stage loop that leaves some pending would make the compiler
+// wait for every LDS read of the common path where it needs only the oldest.
+__device__ __forceinline__ void rare_path_end()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+}
+
+// This lane's index, computed anew where it is called.
+__device__ __forceinline__ int lane_again()
+{
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)unhoisted(0)));
+}
+
+template <int KIND, int ENC>
+__global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
+{
+    using C = T256<KIND>;
+    constexpr int WS = C::WS, XS = C::XS, NW = C::NW, NX = C::NX;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
+    lds_u8 *const lds = (lds_u8 *)smem;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15;
+    const int lg = lane >> 4;
+    const int wn = wave & 3;   // 64-row quarter of the weight tile
+    const int wm = wave >> 2;  // 128-token half of the token tile
+
+    // 1-D grid remapped for the 8 XCDs (block L runs on XCD L % 8): XCD x
+    // takes a contiguous tile range, walked in groups of four weight tiles
+    // with the weight tile fastest, so the ~32 blocks resident on an XCD share
+    // 4 weight tiles and 8 token tiles through its L2.
+    const uint32_t mtiles = (uint32_t)((a.rows + 255) >> 8);
+    const uint32_t ntiles = (uint32_t)((a.n + 255) >> 8);
+    const uint32_t per_split = mtiles * ntiles;
+    const uint32_t total = per_split * (uint32_t)a.splits;
+    const uint32_t per_xcd = (total + 7) / 8;
+    const uint32_t tl = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (tl >= total)
+        return;
+    constexpr uint32_t G = 4;
+    const uint32_t s = tl / per_split;
+    const uint32_t rr = tl % per_split;
+    const uint32_t chunk = rr / (G * mtiles);
+    const uint32_t within = rr % (G * mtiles);
+    const uint32_t gc = ntiles - chunk * G < G ? ntiles - chunk * G : G;
+    const int ntile = (int)(chunk * G + within % gc);
+    const int64_t mrow0 = (int64_t)(within / gc) * 256;
+    const int64_t mrow1 = mrow0 + 256 < a.rows ? mrow0 + 256 : a.rows;
+    const int64_t n0 = (int64_t)ntile * 256;
+    const int64_t kb0 = (int64_t)s * a.ksplit;
+    const int klen = (int)((kb0 + a.ksplit < a.k ? kb0 + a.ksplit : a.k) - kb0);
+    const int ntk = (klen + C::BK - 1) / C::BK;
+    const int t_full = klen / C::BK;  // stages entirely inside the K range
+    // Serpentine K walk (FP16): odd groups of four weight tiles walk K
+    // backwards and so start on the token stages the XCD's previous group read
+    // last, still in its L2 (gate+up at 2048 tokens 0.94x the time in fast
+    // mode, 0.99x in full mode).
+    const bool rev = KIND != T_FP8 && ((ntile >> 2) & 1);
+    auto tk = [&](int t) { return rev ? ntk - 1 - t : t; };
+
+    // ---- DMA sources ---------------------------------------------------------
+    // token instruction jj: rows 8(4w+jj) .. +7, lane -> row + lane/8, slot
+    // lane%8.  Rows past the tile's last token lie beyond the buffer resource.
+    const int64_t xrow0 = mrow0 + 32 * wave < mrow1 ? mrow0 + 32 * wave : mrow1 - 1;
+    const uint8_t *xbase = static_cast<const uint8_t *>(a.x) + (xrow0 * a.k + kb0) * C::XB;
+    const rsrc_t xr = make_rsrc(xbase, ((mrow1 - xrow0) * a.k - kb0) * C::XB);
+    const uint32_t xstep = (uint32_t)(8 * a.k * C::XB);  // eight rows on
+    uint32_t xoff[2];
+#pragma unroll
+    for (int par = 0; par < 2; ++par) {
+        const int slot = (lane & 7) ^ swz8(8 * par + (lane >> 3));
+        xoff[par] = (uint32_t)((lane >> 3) * a.k + (KIND == T_FP8 ? slot * 16 : tok_chunk(slot) * 8)) *
+                    C::XB;
+    }
+    auto issue_x = [&](int tr, int slot) {
+        lds_u8 *dst = lds + C::X_BASE + slot * C::X_SLOT + 4096 * wave;
+        if (tr < t_full) {
+#pragma unroll
+            for (int jj = 0; jj < NX; ++jj)
+                buffer_load_lds(xr, dst + jj * 1024, 16,
+                                                         (uint32_t)unhoisted((int)xoff[jj & 1]) + jj * xstep,
+                                                         tr * (C::BK * C::XB), 0, 0);
+        } else {
+            const int ln = lane_again();
+#pragma unroll
+            for (int jj = 0; jj < NX; ++jj) {
+                const int sl = (ln & 7) ^ swz8(8 * jj + (ln >> 3));
+                const int kk = tr * C::BK + (KIND == T_FP8 ? sl * 16 : tok_chunk(sl) * 8);
+                const int64_t m = mrow0 + 32 * wave + 8 * jj + (ln >> 3);
+                const bool ok = m < mrow1 && kk < klen;
+                const uint8_t *src =
+                    static_cast<const uint8_t *>(a.x) + (m * a.k + kb0 + kk) * C::XB;
+                dma16_at(ok ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
+            }
+            rare_path_end();
+        }
+    };
+    // weight instruction jj: lines 8j .. 8j+7 (j = NW w + jj), lane -> line
+    // 8j + lane/8, slot lane%8
+    auto w_row = [&](int ln, int jj, int &wel, bool &lo) {
+        const int line = 8 * (NW * wave + jj) + (ln >> 3);
+        const int c = (ln & 7) ^ swz8(line);
+        lo = KIND == T_FULL && c >= 4;
+        wel = KIND == T_FP8 ? c * 16 : (c & 3) * 16;
+        const int r = KIND == T_FAST ? (2 * (line >> 4) + (c >> 2)) * 16 + (line & 15) : line;
+        const int64_t nr = n0 + r;
+        return nr < a.n ? nr : a.n - 1;
+    };
+    const int64_t wrow0 = n0 + 32 * wave < a.n ? n0 + 32 * wave : a.n - 1;
+    const rsrc_t wr = make_rsrc(a.hi + wrow0 * a.k + kb0, 0xFFFFFFFFll);
+    uint32_t woff[NW];      // fast mode and FP8: byte offset from wr's base
+    const uint8_t *wp[NW];  // full mode: pointer of the piece of K stage 0
+    int wev = tk(0);        // full mode: next stage whose pieces need new pointers
+    if (KIND != T_FULL)
+#pragma unroll
+        for (int jj = 0; jj < NW; ++jj) {
+            int wel;
+            bool lo;
+            const int64_t nr = w_row(lane, jj, wel, lo);
+            woff[jj] = (uint32_t)((nr > wrow0 ? nr - wrow0 : 0) * a.k + wel);
+        }
+    // Full mode: the pointers of stage tr's pieces, and the next stage in walk
+    // order at which any lane's piece leaves its residual chunk or passes the
+    // end of the K range (pieces without a source read zeros, stage by stage).
+    auto w_pointers = [&](int tr) {
+        const int ln = lane_again();
+        const int64_t off = (int64_t)tr * C::BK;
+        int lo_t = 0, hi_t = ntk;  // stages [lo_t, hi_t) keep these pointers
+#pragma unroll
+        for (int jj = 0; jj < NW; ++jj) {
+            int wel;
+            bool lo;
+            const int64_t nr = w_row(ln, jj, wel, lo);
+            const int64_t l0 = nr * a.k + kb0 + wel;
+            const bool in = off + wel < klen;
+            const uint8_t *p = a.hi + l0;
+            bool ok = in;
+            int t0 = 0, t1 = (klen - wel + C::BK - 1) / C::BK;
+            if (lo) {
+                const int64_t l = l0 + (in ? off : 0);
+                const int64_t o = residual_offset(a.res, l);
+                ok = in && o >= 0;
+                p = a.res.pool + (o - (in ? off : 0));
+                const int64_t cb = (l >> a.res.log2c) << a.res.log2c;
+                const int64_t b0 = (cb - l0 + C::BK - 1) >> 6;
+                const int64_t b1 = (cb + (int64_t(1) << a.res.log2c) - l0 + C::BK - 1) >> 6;
+                t0 = b0 > 0 ? (int)b0 : 0;
+                t1 = b1 < t1 ? (int)b1 : t1;
+            }
+            wp[jj] = ok ? p : g_zero16 - off;
+            t0 = ok ? t0 : tr;
+            t1 = ok ? t1 : tr + 1;
+            lo_t = t0 > lo_t ? t0 : lo_t;
+            hi_t = t1 < hi_t ? t1 : hi_t;
+        }
+        if (__all(lo_t <= 0 && hi_t >= ntk)) {
+            wev = -1;
+            rare_path_end();
+            return;
+        }
+        int v = rev ? -(lo_t - 1) : hi_t;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const int u = __shfl_xor(v, d, 64);
+            v = u < v ? u : v;
+        }
+        v = __builtin_amdgcn_readfirstlane(v);
+        wev = rev ? -v : v;
+        rare_path_end();
+    };
+    static_assert(KIND != T_FULL || C::BK == 64, "stage arithmetic of w_pointers");
+    auto issue_w = [&](int tr, int slot) {
+        lds_u8 *dst = lds + slot * C::W_SLOT + NW * 1024 * wave;
+        if (KIND == T_FULL) {
+#pragma unroll
+            for (int jj = 0; jj < NW; ++jj)
+                dma16_at(wp[jj] + (int64_t)tr * C::BK, dst + jj * 1024);
+        } else if (tr < t_full) {
+#pragma unroll
+            for (int jj = 0; jj < NW; ++jj)
+                buffer_load_lds(wr, dst + jj * 1024, 16,
+                                                         woff[jj], tr * C::BK, 0, 0);
+        } else {
+            const int ln = lane_again();
+#pragma unroll
+            for (int jj = 0; jj < NW; ++jj) {
+                int wel;
+                bool lo;
+                const int64_t nr = w_row(ln, jj, wel, lo);
+                const int kk = tr * C::BK + wel;
+                const uint8_t *src = a.hi + nr * a.k + kb0 + kk;
+                dma16_at(kk < klen ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
+            }
+            rare_path_end();
+        }
+    };
+
+    f32x4 acc[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // ---- fragment reads ---------------------------------------------------------
+    const int aoff0 = (wn * (KIND == T_FAST ? 32 : 64) + li) * 128 + ((lg ^ swz8(li)) << 4);
+    const int aoff1 = (wn * (KIND == T_FAST ? 32 : 64) + li) * 128 + (((4 + lg) ^ swz8(li)) << 4);
+    const int boff0 = C::X_BASE + (wm * 128 + li) * 128 + ((lg ^ swz8(li)) << 4);
+    const int boff1 = C::X_BASE + (wm * 128 + li) * 128 + (((4 + lg) ^ swz8(li)) << 4);
+    u32x4 raw[C::RAW];
+    u32x4 bv[4][2];
+    auto ld = [&](int off) { return *reinterpret_cast<const u32x4 *>(smem + off); };
+    auto read_w = [&](int slot) {
+        const int b = slot * C::W_SLOT;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            if (KIND == T_FAST) {
+                raw[nt] = ld(b + ((nt & 1) ? aoff1 : aoff0) + (nt >> 1) * 2048);
+            } else {
+                raw[nt] = ld(b + aoff0 + nt * 2048);
+                raw[(4 + nt) % C::RAW] = ld(b + aoff1 + nt * 2048);
+            }
+        }
+    };
+    auto read_b = [&](int slot, int mt) {
+        const int b = slot * C::X_SLOT + mt * 2048;
+        bv[mt & 3][0] = ld(b + boff0);
+        bv[mt & 3][1] = ld(b + boff1);
+    };
+
+    // ---- prologue ---------------------------------------------------------------
+#pragma unroll 1
+    for (int u = -WS; u < 0; ++u) {
+        if (u + XS >= 0 && u + XS < ntk)
+            issue_x(tk(u + XS), u + XS);
+        if (u + WS < ntk) {
+            if (KIND == T_FULL && tk(u + WS) == wev)
+                w_pointers(wev);
+            issue_w(tk(u + WS), u + WS);
+        }
+    }
+    if (WS <= ntk)
+        DPS_WAIT_VMCNT(C::OUTSTANDING + NX + NW);
+    else
+        DPS_WAIT_VMCNT(0);
+    stage_barrier();
+    read_w(0);
+    read_b(0, 0);
+    read_b(0, 1);
+
+    // Weight operands of stage t: av[q] feeds MFMA step q.  Step 0's are formed
+    // at the end of stage t - 1, after the last MFMA that reads the old ones,
+    // and step 1's between the first MFMAs of stage t, so the byte merges run
+    // beside matrix work.
+    half8 av[2][4];
+    i32x8 a8[4];
+    auto form = [&](int q) {
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const u32x4 h = raw[nt];
+            const u32x4 l = KIND == T_FULL ? raw[(4 + nt) % C::RAW] : u32x4{0u, 0u, 0u, 0u};
+            constexpr int MODE = KIND == T_FULL ? MODE_FULL : MODE_FAST;
+            if (KIND == T_FP8)
+                a8[nt] = i32x8{(int)h.x, (int)h.y, (int)h.z, (int)h.w,
+                               (int)raw[(4 + nt) % C::RAW].x, (int)raw[(4 + nt) % C::RAW].y,
+                               (int)raw[(4 + nt) % C::RAW].z, (int)raw[(4 + nt) % C::RAW].w};
+            else
+                av[q][nt] = q ? weight8<MODE, ENC>(h.z, h.w, l.z, l.w)
+                              : weight8<MODE, ENC>(h.x, h.y, l.x, l.y);
+        }
+    };
+    auto mma_q = [&](int mt, int q) {  // F16 kinds: MFMA step q of token tile mt
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            acc[nt][mt] = mfma16x16x32(av[q][nt], as_half8(bv[mt & 3][q]), acc[nt][mt]);
+    };
+    auto mma = [&](int mt) {
+        if (KIND == T_FP8) {
+            const u32x4 p = bv[mt & 3][0], q = bv[mt & 3][1];
+            const i32x8 b8 = {(int)p.x, (int)p.y, (int)p.z, (int)p.w,
+                              (int)q.x, (int)q.y, (int)q.z, (int)q.w};
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                acc[nt][mt] = mfma16x16x128_fp8<ENC>(a8[nt], b8, acc[nt][mt]);
+        } else {
+            mma_q(mt, 0);
+            mma_q(mt, 1);
+        }
+    };
+    form(0);
+    int ws = 0, xs = 0;  // slots of stage t
+    int wf = 0;          // weight slot that stage t - 1 left
+    for (int t = 0; t < ntk; ++t) {
+        const int ws1 = ws + 1 < WS ? ws + 1 : 0;
+        const int xs1 = xs + 1 < XS ? xs + 1 : 0;
+#pragma unroll
+        for (int mt = 0; mt < 6; ++mt) {
+            if (mt > 0)
+                __builtin_amdgcn_sched_barrier(0);
+            read_b(xs, mt + 2);
+            if (mt == 0 && KIND != T_FP8) {
+                mma_q(0, 0);
+                form(1);
+                mma_q(0, 1);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+                }
+            } else {
+                mma(mt);
+            }
+            if (mt == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (t > 0 && t - 1 + WS < ntk)
+                    issue_w(tk(t - 1 + WS), wf);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + WS <= ntk)
+            DPS_WAIT_VMCNT(C::OUTSTANDING);
+        else
+            DPS_WAIT_VMCNT(0);
+        stage_barrier();
+        if (KIND == T_FULL && t + WS < ntk && tk(t + WS) == wev)
+            w_pointers(wev);
+        read_w(ws1);
+        read_b(xs1, 0);
+        read_b(xs1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + XS < ntk)
+            issue_x(tk(t + XS), xs);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(6);
+        if (KIND == T_FP8) {
+            mma(7);
+            form(0);
+        } else {
+            mma_q(7, 0);
+            form(0);
+            mma_q(7, 1);
+            __builtin_amdgcn_sched_group_barrier(0x8, 12, 1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 1);
+                __builtin_amdgcn_sched_group_barrier(0x2, 8, 1);
+            }
+        }
+        wf = ws;
+        ws = ws1;
+        xs = xs1;
+    }
+
+    // Lane (i, g) holds rows 16 nt + 4g .. +3 of the wave's 64 weight rows for
+    // token 16 mt + i.  A tile inside the output stores without per-element
+    // checks; every lane's addresses are one pointer plus constants.
+    constexpr float wscale = ENC == ENC_E4M3 ? 0.00390625f : 1.f;
+    const int le = lane_again();
+    const int64_t m = mrow0 + wm * 128 + (le & 15);
+    const int64_t n = n0 + wn * 64 + (le >> 4) * 4;
+    if (KIND == T_FP8) {
+#pragma unroll
+        for (int mt = 0; mt < 8; ++mt) {
+            const float sc = m + 16 * mt < mrow1 ? a.scale[m + 16 * mt] * wscale : 0.f;
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                acc[nt][mt] *= sc;
+        }
+    }
+    if (mrow0 + 256 == mrow1 && n0 + 256 <= a.n && (a.n & 3) == 0) {
+        if (a.splits == 1) {
+            uint16_t *yp = a.y + m * a.n + n;
+#pragma unroll
+            for (int mt = 0; mt < 8; ++mt, yp += 16 * a.n)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    store_half4(yp + nt * 16, acc[nt][mt]);
+        } else {
+            float *pp = a.partial + ((int64_t)s * a.rows + m) * a.n + n;
+#pragma unroll
+            for (int mt = 0; mt < 8; ++mt, pp += 16 * a.n)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    *reinterpret_cast<f32x4 *>(pp + nt * 16) = acc[nt][mt];
+        }
+        return;
+    }
+#pragma unroll
+    for (int mt = 0; mt < 8; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+            store_tile_out(a, s, m + 16 * mt, n + 16 * nt, acc[nt][mt], mrow1);
+}
+
+template <int KIND, int ENC>
+hipError_t launch(const GemmArgs &a, hipStream_t stream)
+{
+    const dim3 grid = dense_grid((a.n + 255) / 256 * a.splits * ((a.rows + 255) / 256));
+    hipLaunchKernelGGL((tile256_kernel<KIND, ENC>), grid, dim3(512), 0, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm256_f16(int mode, int enc, const GemmArgs &a, hipStream_t stream)
+{
+    if (mode == MODE_FULL)
+        return enc == ENC_E4M3 ? launch<T_FULL, ENC_E4M3>(a, stream)
+                               : launch<T_FULL, ENC_E5M2>(a, stream);
+    return enc == ENC_E4M3 ? launch<T_FAST, ENC_E4M3>(a, stream)
+                           : launch<T_FAST, ENC_E5M2>(a, stream);
+}
+
+hipError_t launch_gemm256_fp8(int enc, const GemmArgs &a, hipStream_t stream)
+{
+    return enc == ENC_E4M3 ? launch<T_FP8, ENC_E4M3>(a, stream)
+                           : launch<T_FP8, ENC_E5M2>(a, stream);
+}
+
+}  // namespace dps

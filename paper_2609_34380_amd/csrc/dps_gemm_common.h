@@ -1,0 +1,157 @@
+// dps_gemm_common.h -- what the matrix-core GEMM kernels share: the argument
+// block, the token range of a grouped block, output stores, direct-to-LDS
+// loads and the stage barrier (gfx950).
+#pragma once
+
+#include "dps_internal.h"
+
+namespace dps {
+
+struct GemmArgs {
+    const void *x;  // FP16 [rows][k] or E4M3 [rows][k]
+    const int32_t *offsets;
+    int64_t rows;
+    int64_t experts;
+    const uint8_t *hi;
+    ResidualView res;
+    int64_t n, k, ksplit;
+    int splits;
+    uint16_t *y;
+    float *partial;
+    const float *scale;
+    int rotate;  // wide-row GEMM: start each block's K walk by weight tile (see gemm4)
+};
+
+namespace {
+
+constexpr int BM = 128;  // default token tile of block_rows
+
+// Token range of this block: dense calls use grid.y as the token tile;
+// grouped calls walk the experts' tile counts.  Returns false if no work.
+// With tail > 0 (grouped calls) an expert's last tile also takes up to `tail`
+// rows beyond bm, so an expert of bm + 1 .. bm + tail rows is one tile, not
+// two: its weights are read once.  Such a range [m0, m1) spans more than bm
+// rows; the kernel treats rows m0 + bm .. m1 - 1 as its tail.  The tile
+// count per expert never grows, so the host's grid bound still holds.
+__device__ __forceinline__ bool block_rows(const GemmArgs &a, int64_t &e, int64_t &m0,
+                                           int64_t &m1, int bm = BM, int tail = 0)
+{
+    const int64_t t = blockIdx.y;
+    if (!a.offsets) {
+        e = 0;
+        m0 = t * bm;
+        m1 = m0 + bm < a.rows ? m0 + bm : a.rows;
+        return m0 < m1;
+    }
+    int64_t cum = 0;
+    int64_t prev = 0;
+    for (int64_t ex = 0; ex < a.experts; ++ex) {
+        int64_t o1 = a.offsets[ex + 1];
+        o1 = o1 < prev ? prev : (o1 > a.rows ? a.rows : o1);
+        const int64_t r = o1 - prev;
+        const int64_t tiles =
+            r <= 0 ? 0 : (r <= bm + tail ? 1 : (r - tail + bm - 1) / bm);
+        if (t < cum + tiles) {
+            e = ex;
+            m0 = prev + (t - cum) * bm;
+            m1 = t == cum + tiles - 1 ? o1 : m0 + bm;  // the last tile takes the tail
+            return true;
+        }
+        cum += tiles;
+        prev = o1;
+    }
+    return false;
+}
+
+__device__ __forceinline__ void store_tile_out(const GemmArgs &a, int s, int64_t m, int64_t n0,
+                                               f32x4 v, int64_t m1)
+{
+    if (m >= m1 || n0 >= a.n)
+        return;
+    if (a.splits == 1) {
+        uint16_t *yp = a.y + m * a.n + n0;
+        if (n0 + 3 < a.n && (a.n & 3) == 0) {
+            typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+            half4 hv = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
+            *reinterpret_cast<half4 *>(yp) = hv;
+        } else {
+            const float vv[4] = {v.x, v.y, v.z, v.w};
+            for (int r = 0; r < 4 && n0 + r < a.n; ++r)
+                yp[r] = __builtin_bit_cast(uint16_t, (_Float16)vv[r]);
+        }
+    } else {
+        float *pp = a.partial + ((int64_t)s * a.rows + m) * a.n + n0;
+        if (n0 + 3 < a.n && (a.n & 3) == 0) {
+            *reinterpret_cast<f32x4 *>(pp) = v;
+        } else {
+            const float vv[4] = {v.x, v.y, v.z, v.w};
+            for (int r = 0; r < 4 && n0 + r < a.n; ++r)
+                pp[r] = vv[r];
+        }
+    }
+}
+
+__device__ __attribute__((aligned(16))) const uint8_t g_zero16[16] = {0};
+
+#define DPS_LDS(p) ((__attribute__((address_space(3))) void *)(p))
+
+__device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
+{
+    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, 0);
+}
+
+// The same, 16 bytes per lane from `src` into the wave's 1 KiB at LDS address
+// `lds` (lane l lands at lds + 16 l), as one asm statement without outputs.
+// The compiler takes the builtin for a flat access that may retire out of
+// order and then waits for lgkmcnt(0) before every use of an LDS read, where
+// the reads still in flight could stay so.  Completion is the caller's own
+// business (vmcnt, in issue order).
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+
+__device__ __forceinline__ void dma16_at(const void *src, lds_u8 *lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"((uint32_t)(uintptr_t)lds), "v"(src)
+                 : "memory", "m0");
+}
+
+// s_waitcnt vmcnt(n) leaving the other counters alone (gfx9 encoding).
+#define DPS_WAIT_VMCNT(n) \
+    __builtin_amdgcn_s_waitcnt(((n) & 0xF) | ((((n) >> 4) & 3) << 14) | (0x7 << 4) | (0xF << 8))
+
+// Block barrier between pipeline stages.  __syncthreads() carries a
+// workgroup-scope fence, which the compiler satisfies by waiting for every
+// outstanding vector-memory operation (direct-to-LDS loads count as LDS
+// writes): the whole DMA ring would drain at every stage.  The loops instead
+// wait for exactly what they need -- their own DMA of the stage about to be
+// read (vmcnt, before this call) and their own LDS reads of the slot about to
+// be refilled (lgkmcnt(0), here) -- and then meet at a bare s_barrier.  The
+// empty asm statements keep the compiler from moving memory accesses across.
+__device__ __forceinline__ void stage_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt at their maxima
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Swizzle of 128-byte LDS rows: 16-byte chunk c of row r sits at slot
+// c ^ swz8(r).  Lane (i, g) reading chunk 4q + g of 16 such rows is the
+// pattern measured conflict-free (ds_read_b128 at ~210 B/clk per CU).
+__device__ __forceinline__ int swz8(int r) { return (r >> 1) & 7; }
+
+// dense calls: a 1-D grid, padded to a multiple of the 8 XCDs
+inline dim3 dense_grid(int64_t tiles)
+{
+    return dim3((unsigned)((tiles + 7) / 8 * 8), 1, 1);
+}
+
+}  // namespace
+
+// The 256 x 256 tile (dps_gemm256.hip): FP16 full and fast mode, and FP8
+// activations.
+hipError_t launch_gemm256_f16(int mode, int enc, const GemmArgs &a, hipStream_t stream);
+hipError_t launch_gemm256_fp8(int enc, const GemmArgs &a, hipStream_t stream);
+
+}  // namespace dps
