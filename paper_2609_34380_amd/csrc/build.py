@@ -19,8 +19,7 @@ LIB = os.path.join(PKG, "libdps.so")
 PROBE_LIB = os.path.join(PKG, "libdps_probe.so")
 PROBE_SOURCES = ["dps_probe.hip"]
 SOURCES = ["dps_elementwise.hip", "dps_skinny.hip", "dps_gemv.hip", "dps_rows.hip", "dps_gemm.hip",
-           "dps_gemm256.hip",
-           "dps_restore.hip", "dps_api.hip", "dps_sum.cpp", "dps_vmm.hip",
+           "dps_gemm256.hip", "dps_restore.hip", "dps_api.hip", "dps_sum.cpp", "dps_vmm.hip",
            "dps_worker.hip"]
 ARCH = "gfx950"
 
@@ -38,7 +37,8 @@ CFLAGS = [
 # in a streaming or matrix-core kernel adds memory traffic beside the weight
 # stream and costs time with no error, so the build fails on it instead.
 NO_SCRATCH = {"dps_elementwise.hip", "dps_skinny.hip", "dps_gemv.hip", "dps_rows.hip",
-              "dps_gemm.hip", "dps_gemm256.hip", "dps_probe.hip"}
+              "dps_gemm.hip", "dps_gemm256.hip",
+              "dps_probe.hip"}
 
 
 def _scratch_users(report):

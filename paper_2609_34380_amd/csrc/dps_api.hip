@@ -142,10 +142,6 @@ dps_status check_weight(const dps_weight *w, int mode)
 
 namespace dps {
 
-// The 256 x 256 tile addresses the 32 rows a wave loads with 32-bit byte
-// offsets.
-constexpr int64_t kMaxTile256K = int64_t(1) << 25;
-
 LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_t k,
                        int64_t experts, int log2c, int cu_count, bool grouped)
 {
@@ -165,8 +161,7 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         {
             const int64_t cus = cu_count;
             const int64_t big = cdiv(n, 256) * cdiv(rows, 256);
-            const bool fills = big >= cus && (big % cus == 0 || 2 * (big % cus) >= cus) &&
-                               k <= kMaxTile256K;
+            const bool fills = big >= cus && (big % cus == 0 || 2 * (big % cus) >= cus);
             p.variant = fills && !grouped ? GEMM_G3_256x256 : GEMM_G3_256x128;
         }
         // K is split only while the tiles alone leave CUs idle: the fp32
@@ -269,7 +264,7 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         // tokens (192 and 128 tiles, 4-5%), down at 512 / 1024 tokens (8 / 4
         // ranges: 89 / 161 against 80 / 154 us) and every decode call up to
         // 256 tokens (gate+up at 256 tokens 93 against 88 us).
-        if (!grouped && rows >= 512 && k <= kMaxTile256K) {
+        if (!grouped && rows >= 512) {
             const int64_t t5 = cdiv(n, 256) * cdiv(rows, 256);
             if (t5 >= cu_count || (k >= 8192 && 2 * t5 >= cu_count))
                 p.variant = GEMM_G5_256x256;

@@ -383,7 +383,7 @@ __device__ __forceinline__ int swz16(int r) { return r & 15; }
 // 16-row weight sub-tiles of their quarter and waves of half 1 on the other
 // two, so every compute wave does 36 MFMAs per stage instead of 32.  The
 // tail's K-half sums go through LDS with the others.
-template <int MODE, int ENC, int BM, int WS, int XS, bool RANGE, bool SPEC, int TAIL = 0>
+template <int MODE, int ENC, int BM, int WS, int XS, bool RANGE, bool SPEC, int AUX, int TAIL = 0>
 __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
 {
     using C = G4<MODE, BM, WS, XS, SPEC ? 4 : 8>;
@@ -417,24 +417,23 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
         // within the group, so the ~32 blocks resident on an XCD cover about
         // 4 weight tiles x 8 token tiles and both operands are re-read from
         // that XCD's L2 rather than from HBM.
-        const int64_t mtiles = (a.rows + BM - 1) / BM;
-        const int64_t ntiles = (a.n + 127) / 128;
-        const int64_t total = mtiles * ntiles * a.splits;
-        const int64_t per_xcd = (total + 7) / 8;
-        const int64_t lin = blockIdx.x;
-        const int64_t t = (lin % 8) * per_xcd + lin / 8;
+        // (Tile counts fit 32 bits: the grid does.)
+        const uint32_t mtiles = (uint32_t)((a.rows + BM - 1) / BM);
+        const uint32_t ntiles = (uint32_t)((a.n + 127) / 128);
+        const uint32_t total = mtiles * ntiles * (uint32_t)a.splits;
+        const uint32_t per_xcd = (total + 7) / 8;
+        const uint32_t t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
         if (t >= total)
             return;
-        constexpr int64_t G = 4;
+        constexpr uint32_t G = 4;
         s = (int)(t / (mtiles * ntiles));
-        const int64_t r = t % (mtiles * ntiles);
-        const int64_t chunk = r / (G * mtiles);
-        const int64_t within = r % (G * mtiles);
-        const int64_t gc = ntiles - chunk * G < G ? ntiles - chunk * G : G;
-        const int64_t mt = within / gc;
+        const uint32_t r = t % (mtiles * ntiles);
+        const uint32_t chunk = r / (G * mtiles);
+        const uint32_t within = r % (G * mtiles);
+        const uint32_t gc = ntiles - chunk * G < G ? ntiles - chunk * G : G;
         ntile = (int)(chunk * G + within % gc);
         e = 0;
-        mrow0 = mt * BM;
+        mrow0 = (int64_t)(within / gc) * BM;
         mrow1 = mrow0 + BM < a.rows ? mrow0 + BM : a.rows;
         mtail1 = mrow1;
     }
@@ -520,7 +519,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     // the same order, so they still meet in L2.  (MI355X, gate+up 28672 x
     // 4096 in full mode: 0.78x the time at 32 tokens, 0.83x at 128, 0.91x at
     // 256; the other hidden-4096 layers within 3%.)
-    const int64_t grot = a.rotate && ntk > 0 ? (int64_t)(ntile >> 2) % ntk : 0;
+    const int64_t grot = a.rotate && ntk > 0 ? (uint32_t)(ntile >> 2) % (uint32_t)ntk : 0;
     auto tk = [&](int64_t t) {
         return t < ntk ? (t + grot < ntk ? t + grot : t + grot - ntk) : t;
     };
@@ -534,7 +533,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
         const int64_t off = tr * C::BK;
         const int j = issuer * C::W_INSTR + jj;
         const bool ok = !masked || off < wlim[jj];
-        dma16(ok ? (const void *)(wp[jj] + off) : (const void *)g_zero16, st + j * 1024);
+        dma16<AUX>(ok ? (const void *)(wp[jj] + off) : (const void *)g_zero16, st + j * 1024);
         if (MODE == MODE_FULL) {
             const void *src = g_zero16;
             if (RANGE) {
@@ -548,7 +547,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
                 if (ok && o >= 0)
                     src = a.res.pool + o;
             }
-            dma16(src, st + C::W_BYTES + j * 1024);
+            dma16<AUX>(src, st + C::W_BYTES + j * 1024);
         }
     };
     auto issue_x1 = [&](int jj, int64_t t) {
@@ -699,37 +698,50 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     DPS_WAIT_VMCNT(0);  // no DMA may still target this block's LDS
     __syncthreads();    // every wave is done reading the stages
 
-    // K-half 1 hands its partial sums to K-half 0 through LDS (4 KB per tile)
+    // Each K half hands two of its four row tiles to the other through LDS (4
+    // KB per tile), so both halves add and store; every sum is half 0 plus
+    // half 1.  The tail's sums go to half 0.
     constexpr int RED = 4 * C::MT + (TAIL > 0 ? 2 : 0);  // 16 x 16 tiles per wave
     static_assert(4 * RED * 64 * 16 <= C::LDS, "K-half reduction area");
     f32x4 *red = reinterpret_cast<f32x4 *>(smem) + (wave & 3) * (RED * 64);
-    if (kh == 1) {
+    const int khu = __builtin_amdgcn_readfirstlane(kh);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < 4; ++nt)
+        if ((nt >> 1) != khu)
 #pragma unroll
             for (int mt = 0; mt < C::MT; ++mt)
                 red[(nt * C::MT + mt) * 64 + lane] = acc[nt][mt];
-        if (TAIL > 0 && has_tail) {
-            red[(4 * C::MT) * 64 + lane] = tacc[0];
-            red[(4 * C::MT + 1) * 64 + lane] = tacc[1];
-        }
+    if (TAIL > 0 && has_tail && khu == 1) {
+        red[(4 * C::MT) * 64 + lane] = tacc[0];
+        red[(4 * C::MT + 1) * 64 + lane] = tacc[1];
     }
     __syncthreads();
-    if (kh == 1)
-        return;
+    const int64_t m = mrow0 + wm * (BM / 2) + li;
+    const int64_t n = n0 + wn * 64 + lg * 4;
+    // a tile inside the output stores without per-element checks
+    const bool whole = mrow0 + BM == mrow1 && n0 + 128 <= a.n && (a.n & 3) == 0;
 #pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) {
-        const int64_t m = mrow0 + wm * (BM / 2) + mt * 16 + li;
+    for (int nt = 0; nt < 4; ++nt) {
+        if ((nt >> 1) != khu)
+            continue;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            store_tile_out(a, s, m, n0 + wn * 64 + nt * 16 + lg * 4,
-                           acc[nt][mt] + red[(nt * C::MT + mt) * 64 + lane], mrow1);
+        for (int mt = 0; mt < C::MT; ++mt) {
+            const f32x4 o = red[(nt * C::MT + mt) * 64 + lane];
+            const f32x4 v = acc[nt][mt] + o;
+            if (whole && a.splits == 1)
+                store_half4(a.y + (m + 16 * mt) * a.n + n + 16 * nt, v);
+            else if (whole)
+                *reinterpret_cast<f32x4 *>(a.partial + ((int64_t)s * a.rows + m + 16 * mt) * a.n +
+                                           n + 16 * nt) = v;
+            else
+                store_tile_out(a, s, m + 16 * mt, n + 16 * nt, v, mrow1);
+        }
     }
-    if (TAIL > 0 && has_tail) {
-        const int64_t m = mrow0 + BM + li;
+    if (TAIL > 0 && has_tail && khu == 0) {
+        const int64_t mt = mrow0 + BM + li;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            store_tile_out(a, s, m, n0 + wn * 64 + (2 * wmu + j) * 16 + lg * 4,
+            store_tile_out(a, s, mt, n0 + wn * 64 + (2 * wmu + j) * 16 + lg * 4,
                            tacc[j] + red[(4 * C::MT + j) * 64 + lane], mtail1);
     }
 }
@@ -790,35 +802,43 @@ hipError_t launch_g3_variant(const GemmArgs &a, const LinearPlan &plan, hipStrea
 
 // Grouped calls on the 128-token tile with DMA waves take up to 16 tail rows
 // per expert into its last tile (gemm4_kernel, block_rows): an expert of
-// 129-144 rows reads its weights once, not twice.
-template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC>
-hipError_t launch_g4(const GemmArgs &a, const LinearPlan &plan, bool grouped, hipStream_t stream)
+// 129-144 rows reads its weights once, not twice.  Every mode and encoding
+// fits the tail's 16 registers within the 168 that three waves per SIMD allow.
+template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC, int AUX>
+hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped,
+                         hipStream_t stream)
 {
     const int64_t nt = (a.n + 127) / 128;
     const dim3 grid = grouped ? dim3((unsigned)(nt * plan.splits),
                                      (unsigned)token_tiles(a.rows, a.experts, true, BM), 1)
                               : dense_grid(nt * plan.splits * ((a.rows + BM - 1) / BM));
     const dim3 block(SPEC ? 768 : 512);
-    // every mode and encoding fits the tail's 16 registers within the 168
-    // that three waves per SIMD allow (E4M3 full mode since its conversion-
-    // based merge; the bit-move merge spilled)
     constexpr int TL = SPEC && BM == 128 ? 16 : 0;
     if (MODE == MODE_FULL && plan.range_addr) {
         if (TL > 0 && grouped)
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC, TL>), grid, block,
-                               0, stream, a);
-        else
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC>), grid, block, 0,
-                               stream, a);
-    } else {
-        if (TL > 0 && grouped)
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC, TL>), grid,
+            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC, AUX, TL>), grid,
                                block, 0, stream, a);
         else
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC>), grid, block,
-                               0, stream, a);
+            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC, AUX>), grid,
+                               block, 0, stream, a);
+    } else {
+        if (TL > 0 && grouped)
+            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC, AUX, TL>), grid,
+                               block, 0, stream, a);
+        else
+            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC, AUX>), grid,
+                               block, 0, stream, a);
     }
     return hipGetLastError();
+}
+
+template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC>
+hipError_t launch_g4(const GemmArgs &a, const LinearPlan &plan, bool grouped, hipStream_t stream)
+{
+    const int64_t planes = MODE == MODE_FULL ? 2 : 1;
+    return a.experts * a.n * a.k * planes >= kStreamBytes
+               ? launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, AUX_STREAM>(a, plan, grouped, stream)
+               : launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, AUX_CACHED>(a, plan, grouped, stream);
 }
 
 // (token tile, weight slots, token slots) per mode, each within 160 KiB:

@@ -43,14 +43,6 @@ namespace dps {
 
 namespace {
 
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ void store_half4(uint16_t *p, f32x4 v)
-{
-    *reinterpret_cast<half4 *>(p) = half4{(_Float16)v.x, (_Float16)v.y, (_Float16)v.z,
-                                          (_Float16)v.w};
-}
-
 enum { T_FULL = 0, T_FAST = 1, T_FP8 = 2 };
 
 // Rings of WS weight and XS token stages.
@@ -87,47 +79,6 @@ struct T256 {
 // tok_chunk is sigma's inverse, the chunk the DMA writes into a slot.
 // Either way both operands of an MFMA pair the same K elements.
 __device__ __forceinline__ int tok_chunk(int slot) { return ((slot & 3) << 1) | (slot >> 2); }
-
-// A raw buffer over [p, p + bytes): 48-bit base, byte count, data format 32
-// (the descriptor of untyped buffers on gfx9).  Loads past the end return zero.
-typedef int32_t rsrc_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *p, int64_t bytes)
-{
-    const uint64_t b = (uint64_t)p;
-    return rsrc_t{__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
-                  __builtin_amdgcn_readfirstlane((int)((b >> 32) & 0xFFFFu)),
-                  __builtin_amdgcn_readfirstlane((int)(bytes < 0xFFFFFFFFll ? bytes : 0xFFFFFFFFll)),
-                  0x00020000};
-}
-
-// buffer_load_dwordx4 ... lds: 16 bytes per lane from buffer offset voffset +
-// soffset into the wave's 1 KiB at `lds`.
-__device__ void buffer_load_lds(rsrc_t rsrc, __attribute__((address_space(3))) void *lds, int size,
-                                int voffset, int soffset, int offset,
-                                int aux) __asm("llvm.amdgcn.raw.buffer.load.lds");
-
-// The value, opaque to the optimizer: what the rare paths of the stage loop
-// derive from it is computed there instead of being kept in registers.
-__device__ __forceinline__ int unhoisted(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
-// lgkmcnt(0).  Scalar loads retire out of order with LDS reads, and a rare
-// path of the stage loop that leaves some pending would make the compiler
-// wait for every LDS read of the common path where it needs only the oldest.
-__device__ __forceinline__ void rare_path_end()
-{
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-}
-
-// This lane's index, computed anew where it is called.
-__device__ __forceinline__ int lane_again()
-{
-    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)unhoisted(0)));
-}
 
 template <int KIND, int ENC>
 __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
@@ -169,7 +120,8 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
     const int64_t kb0 = (int64_t)s * a.ksplit;
     const int klen = (int)((kb0 + a.ksplit < a.k ? kb0 + a.ksplit : a.k) - kb0);
     const int ntk = (klen + C::BK - 1) / C::BK;
-    const int t_full = klen / C::BK;  // stages entirely inside the K range
+    // stages entirely inside the K range, whose loads take 32-bit row offsets
+    const int t_full = a.k <= kMaxOffsetK ? klen / C::BK : 0;
     // Serpentine K walk (FP16): odd groups of four weight tiles walk K
     // backwards and so start on the token stages the XCD's previous group read
     // last, still in its L2 (gate+up at 2048 tokens 0.94x the time in fast

@@ -3,6 +3,8 @@
 // loads and the stage barrier (gfx950).
 #pragma once
 
+#include <type_traits>
+
 #include "dps_internal.h"
 
 namespace dps {
@@ -63,6 +65,14 @@ __device__ __forceinline__ bool block_rows(const GemmArgs &a, int64_t &e, int64_
     return false;
 }
 
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void store_half4(uint16_t *p, f32x4 v)
+{
+    *reinterpret_cast<half4 *>(p) = half4{(_Float16)v.x, (_Float16)v.y, (_Float16)v.z,
+                                          (_Float16)v.w};
+}
+
 __device__ __forceinline__ void store_tile_out(const GemmArgs &a, int s, int64_t m, int64_t n0,
                                                f32x4 v, int64_t m1)
 {
@@ -71,9 +81,7 @@ __device__ __forceinline__ void store_tile_out(const GemmArgs &a, int s, int64_t
     if (a.splits == 1) {
         uint16_t *yp = a.y + m * a.n + n0;
         if (n0 + 3 < a.n && (a.n & 3) == 0) {
-            typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-            half4 hv = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
-            *reinterpret_cast<half4 *>(yp) = hv;
+            store_half4(yp, v);
         } else {
             const float vv[4] = {v.x, v.y, v.z, v.w};
             for (int r = 0; r < 4 && n0 + r < a.n; ++r)
@@ -95,9 +103,14 @@ __device__ __attribute__((aligned(16))) const uint8_t g_zero16[16] = {0};
 
 #define DPS_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 
+// Cache policies of a direct-to-LDS load: plain, and nontemporal for the
+// weights of layers beyond kStreamBytes.
+enum { AUX_CACHED = 0, AUX_STREAM = 2 };
+
+template <int AUX = AUX_CACHED>
 __device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
 {
-    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, AUX);
 }
 
 // The same, 16 bytes per lane from `src` into the wave's 1 KiB at LDS address
@@ -114,6 +127,47 @@ __device__ __forceinline__ void dma16_at(const void *src, lds_u8 *lds)
                  :
                  : "s"((uint32_t)(uintptr_t)lds), "v"(src)
                  : "memory", "m0");
+}
+
+// A raw buffer over [p, p + bytes): 48-bit base, byte count, data format 32
+// (the descriptor of untyped buffers on gfx9).  Loads past the end return zero.
+typedef int32_t rsrc_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void *p, int64_t bytes)
+{
+    const uint64_t b = (uint64_t)p;
+    return rsrc_t{__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
+                  __builtin_amdgcn_readfirstlane((int)((b >> 32) & 0xFFFFu)),
+                  __builtin_amdgcn_readfirstlane((int)(bytes < 0xFFFFFFFFll ? bytes : 0xFFFFFFFFll)),
+                  0x00020000};
+}
+
+// buffer_load_dwordx4 ... lds: 16 bytes per lane from buffer offset voffset +
+// soffset into the wave's 1 KiB at `lds`.
+__device__ void buffer_load_lds(rsrc_t rsrc, __attribute__((address_space(3))) void *lds, int size,
+                                int voffset, int soffset, int offset,
+                                int aux) __asm("llvm.amdgcn.raw.buffer.load.lds");
+
+// The value, opaque to the optimizer: what the rare paths of the stage loop
+// derive from it is computed there instead of being kept in registers.
+__device__ __forceinline__ int unhoisted(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// lgkmcnt(0).  Scalar loads retire out of order with LDS reads, and a rare
+// path of the stage loop that leaves some pending would make the compiler
+// wait for every LDS read of the common path where it needs only the oldest.
+__device__ __forceinline__ void rare_path_end()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+}
+
+// This lane's index, computed anew where it is called.
+__device__ __forceinline__ int lane_again()
+{
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)unhoisted(0)));
 }
 
 // s_waitcnt vmcnt(n) leaving the other counters alone (gfx9 encoding).
@@ -140,6 +194,11 @@ __device__ __forceinline__ void stage_barrier()
 // c ^ swz8(r).  Lane (i, g) reading chunk 4q + g of 16 such rows is the
 // pattern measured conflict-free (ds_read_b128 at ~210 B/clk per CU).
 __device__ __forceinline__ int swz8(int r) { return (r >> 1) & 7; }
+
+// Rows of up to this many elements are reached by 32-bit byte offsets from the
+// first row a wave loads (at most 31 rows of two bytes per element on); longer
+// ones take the general path of the stage loads, with 64-bit addresses.
+constexpr int64_t kMaxOffsetK = int64_t(1) << 25;
 
 // dense calls: a 1-D grid, padded to a multiple of the 8 XCDs
 inline dim3 dense_grid(int64_t tiles)

@@ -104,7 +104,7 @@ struct RowsConfig {
 // NT: 16-token tiles (tokens <= 16 NT); G: 16-row groups per block; RANGE:
 // residual chunks of >= 1 KiB, so that one row piece spans at most two
 // chunks (else a per-vector table lookup).
-template <int MODE, int ENC, int NT, int G, bool RANGE>
+template <int MODE, int ENC, int NT, int G, bool RANGE, int AUX>
 __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
 {
     using C = RowsConfig<MODE, NT, G>;
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
                         src = a.res.pool + off;
                 }
                 __builtin_amdgcn_global_load_lds(
-                    src, DPS_ROWS_LDS(slot + pl * 16 * kRowsKC + ri * kRowsKC), 16, 0, 0);
+                    src, DPS_ROWS_LDS(slot + pl * 16 * kRowsKC + ri * kRowsKC), 16, 0, AUX);
             }
     };
 
@@ -349,15 +349,24 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
     }
 }
 
-template <int MODE, int ENC, int NT, int G>
-hipError_t launch_g(const RowsArgs &a, bool range, hipStream_t stream)
+// AUX: cache policy of the weight loads (kStreamBytes).
+template <int MODE, int ENC, int NT, int G, int AUX>
+hipError_t launch_aux(const RowsArgs &a, bool range, hipStream_t stream)
 {
     const dim3 grid((unsigned)((a.n + 16 * G - 1) / (16 * G)));
     if (MODE == MODE_FULL && !range)
-        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, false>), grid, dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, false, AUX>), grid, dim3(512), 0, stream, a);
     else
-        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, true>), grid, dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, true, AUX>), grid, dim3(512), 0, stream, a);
     return hipGetLastError();
+}
+
+template <int MODE, int ENC, int NT, int G>
+hipError_t launch_g(const RowsArgs &a, bool range, hipStream_t stream)
+{
+    return a.n * a.k * (MODE == MODE_FULL ? 2 : 1) >= kStreamBytes
+               ? launch_aux<MODE, ENC, NT, G, 2>(a, range, stream)
+               : launch_aux<MODE, ENC, NT, G, 0>(a, range, stream);
 }
 
 template <int MODE, int ENC, int NT>
