@@ -264,9 +264,26 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         // tokens (192 and 128 tiles, 4-5%), down at 512 / 1024 tokens (8 / 4
         // ranges: 89 / 161 against 80 / 154 us) and every decode call up to
         // 256 tokens (gate+up at 256 tokens 93 against 88 us).
-        if (!grouped && rows >= 512) {
+        //
+        // Beyond that it takes calls of more than 256 tokens whose 128 x 128
+        // tiles leave a last round of blocks part full, if one or more K
+        // ranges of at least 2048 elements give its own tiles more than half
+        // of the CUs.  Full mode against the 128 x 128 tile: QKV at 1531 tokens
+        // (144 tiles) 110 against 131 us and at 1024 (96, two ranges) 79
+        // against 87, O and down at 1531 (96, two ranges) 75 / 201 against 83 /
+        // 260, gate+up at 512 / 300 (224) 131 / 125 against 178 / 138.  Not O
+        // at 1024 tokens (64 tiles, four ranges of 1024: 56 against 47) or
+        // QKV at 512 (48: 51 against 43).
+        if (!grouped && rows > 256) {
+            const int64_t cus = cu_count;
             const int64_t t5 = cdiv(n, 256) * cdiv(rows, 256);
-            if (t5 >= cu_count || (k >= 8192 && 2 * t5 >= cu_count))
+            const int64_t t4 = cdiv(n, 128) * cdiv(rows, 128);
+            int64_t ranges = cus / t5;
+            ranges = ranges < k / 2048 ? ranges : k / 2048;
+            ranges = ranges < 1 ? 1 : (ranges > 4 ? 4 : ranges);
+            if (rows >= 512 && (t5 >= cus || (k >= 8192 && 2 * t5 >= cus)))
+                p.variant = GEMM_G5_256x256;
+            else if (t5 < cus && t4 > cus && t4 % cus != 0 && 2 * t5 * ranges > cus)
                 p.variant = GEMM_G5_256x256;
         }
         const bool g5 = p.variant == GEMM_G5_256x256;
@@ -275,7 +292,8 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         // the 256-row tiles hold one block per CU (160 KiB of LDS); the
         // wide-row GEMM's eight waves share a CU with others
         int64_t s = (int64_t)cu_count / tiles;
-        const int64_t smax = k / 1024 > 1 ? k / 1024 : 1;
+        const int64_t kmin = g5 ? 2048 : 1024;
+        const int64_t smax = k / kmin > 1 ? k / kmin : 1;
         s = s < 1 ? 1 : (s > smax ? smax : s);
         p.ksplit = round_up(cdiv(k, s), g5 ? 64 : 128);
         p.splits = (int)cdiv(k, p.ksplit);

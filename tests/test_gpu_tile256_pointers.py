@@ -53,3 +53,20 @@ def test_slots_outside_the_pool_read_as_zero(log2c):
     got = dps.linear(x, dps.NestedWeight(nst.nw.hi, dps.Residual(nst.res.pool, bad, log2c)),
                      dps.MODE_FULL)
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("m,n,k,splits", [
+    (300, 16650, 464, 1),     # 132 tiles just past one token tile, ragged every way
+    (700, 8190, 4112, 2),     # 96 tiles in two K ranges, N not a multiple of 4
+])
+@pytest.mark.parametrize("mode", [dps.MODE_FAST, dps.MODE_FULL], ids=["fast", "full"])
+def test_part_filled_grids_take_the_tile(m, n, k, splits, mode):
+    p = dps.plan_info(mode, "fp16", m, n, k)
+    assert (p["tile_rows"], p["tile_tokens"], p["splits"]) == (256, 256, splits)
+    nst = Nested(workloads.weight_fp16(n, k, seed=81), 14, slot_seed=3)
+    x = workloads.activations_fp16(m, k, seed=82)
+    y = dps.linear(x.to(DEV), nst.nw, mode)
+    rows = np.concatenate([np.arange(0, m, 37), [m - 1]])
+    ref = oracle.linear_rows(oracle.FAST if mode == dps.MODE_FAST else oracle.FULL, u16(x), rows,
+                             nst.hi_ref, nst.res_ref if mode == dps.MODE_FULL else None)
+    assert_close(y[torch.from_numpy(rows).to(DEV)], ref)
