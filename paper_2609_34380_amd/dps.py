@@ -6,6 +6,7 @@ turns status codes into exceptions.  PyTorch provides device memory and
 streams, nothing else.  If libdps.so is not built, the first call raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -166,11 +167,13 @@ def _check(status):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The raw handle of torch's current stream on the current device (an int;
+    building torch's Stream object costs a microsecond a call)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _require_cuda(*tensors):
@@ -223,7 +226,14 @@ class NestedWeight:
         if self._c is None:
             res = self.residual.c() if self.residual is not None else _null_residual()
             self._c = CWeight(self.hi.data_ptr(), res, self.experts, self.n, self.k, self.enc)
+            self._ref = ctypes.byref(self._c)
         return self._c
+
+    def ref(self):
+        """byref(c()), made once: the descriptor as the C calls take it."""
+        if self._c is None:
+            self.c()
+        return self._ref
 
 
 def select_enc(w, out=None):
@@ -341,8 +351,15 @@ def _act_flag(act):
     raise ValueError("act must be 'fp16' or 'fp8'")
 
 
+@functools.lru_cache(maxsize=1024)
+def _workspace_need(mode, flag, rows, n, k, experts, device_index):
+    """workspace_bytes() of a shape on the current device (the plan depends
+    on the device's CU count alone)."""
+    return workspace_bytes(mode, flag, rows, n, k, experts)
+
+
 def _workspace(mode, flag, rows, nw, device, workspace):
-    need = workspace_bytes(mode, flag, rows, nw.n, nw.k, nw.experts)
+    need = _workspace_need(mode, flag, rows, nw.n, nw.k, nw.experts, torch.cuda.current_device())
     if need == 0:
         return None, 0
     if workspace is None:
@@ -352,16 +369,19 @@ def _workspace(mode, flag, rows, nw, device, workspace):
 
 def linear(x, nw, mode, act="fp16", out=None, workspace=None):
     """Y = X . W^T through dps_linear; mode MODE_FULL or MODE_FAST."""
-    lib = load_library()
-    _require_cuda(x)
+    lib = _lib or load_library()
+    if not x.is_cuda:
+        _require_cuda(x)
     assert x.dtype == torch.float16 and x.dim() == 2 and x.is_contiguous()
     flag = _act_flag(act)
     m = x.shape[0]
     if out is None:
-        out = torch.empty((m, nw.n), dtype=torch.float16, device=x.device)
+        out = x.new_empty((m, nw.n))
     ws, ws_bytes = _workspace(mode, flag, m, nw, x.device, workspace)
-    _check(lib.dps_linear(mode, flag, _ptr(x), m, ctypes.byref(nw.c()), _ptr(out), _ptr(ws),
-                          ws_bytes, _stream()))
+    status = lib.dps_linear(mode, flag, x.data_ptr(), m, nw.ref(), out.data_ptr(), _ptr(ws),
+                            ws_bytes, _stream())
+    if status:
+        _check(status)
     return out
 
 
@@ -379,7 +399,7 @@ def linear_static(x, nw, mode, act="fp16", out=None):
     m = x.shape[0]
     if out is None:
         out = torch.empty((m, nw.n), dtype=torch.float16, device=x.device)
-    _check(lib.dps_linear_static(mode, flag, _ptr(x), m, ctypes.byref(nw.c()), _ptr(out),
+    _check(lib.dps_linear_static(mode, flag, _ptr(x), m, nw.ref(), _ptr(out),
                                  _stream()))
     return out
 
@@ -396,8 +416,7 @@ def linear_grouped(x_sorted, offsets, nw, mode, act="fp16", out=None, workspace=
         out = torch.empty((rows, nw.n), dtype=torch.float16, device=x_sorted.device)
     ws, ws_bytes = _workspace(mode, flag, rows, nw, x_sorted.device, workspace)
     _check(lib.dps_linear_grouped(mode, flag, _ptr(x_sorted), _ptr(offsets), rows,
-                                  ctypes.byref(nw.c()), _ptr(out), _ptr(ws), ws_bytes,
-                                  _stream()))
+                                  nw.ref(), _ptr(out), _ptr(ws), ws_bytes, _stream()))
     return out
 
 
