@@ -383,16 +383,17 @@ __device__ __forceinline__ int swz16(int r) { return r & 15; }
 // 16-row weight sub-tiles of their quarter and waves of half 1 on the other
 // two, so every compute wave does 36 MFMAs per stage instead of 32.  The
 // tail's K-half sums go through LDS with the others.
-template <int MODE, int ENC, int BM, int WS, int XS, bool RANGE, bool SPEC, int AUX, int TAIL = 0>
+template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC, int AUX, int TAIL = 0>
 __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
 {
     using C = G4<MODE, BM, WS, XS, SPEC ? 4 : 8>;
     static_assert(TAIL == 0 || (TAIL == 16 && SPEC && BM == 128), "tail rows: 128-token DMA-wave tile");
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
+    lds_u8 *const lds = (lds_u8 *)smem;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15;
     const int lg = lane >> 4;
     const bool dma_wave = SPEC && wave >= 8;
@@ -440,7 +441,19 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     const int64_t n0 = (int64_t)ntile * 128;
     const int64_t kb0 = (int64_t)s * a.ksplit;
     const int64_t ke = kb0 + a.ksplit < a.k ? kb0 + a.ksplit : a.k;
-    const int64_t ntk = ke > kb0 ? (ke - kb0 + C::BK - 1) / C::BK : 0;
+    const int klen = (int)(ke - kb0);
+    const int ntk = (klen + C::BK - 1) / C::BK;
+    // stages entirely inside the K range, whose loads take 32-bit row offsets
+    const int t_full = a.k <= kMaxOffsetK ? klen / C::BK : 0;
+    // Iteration t stages K range tk(t).  With rows a multiple of 4 KiB apart,
+    // blocks walking their K ranges in step would all touch the same 128-byte
+    // column (address bits 7-11) at once; each group of four weight tiles
+    // starts at another stage instead.  Token tiles of one weight tile keep
+    // the same order, so they still meet in L2.  (MI355X, gate+up 28672 x
+    // 4096 in full mode: 0.78x the time at 32 tokens, 0.83x at 128, 0.91x at
+    // 256; the other hidden-4096 layers within 3%.)
+    const int grot = a.rotate ? (int)((uint32_t)(ntile >> 2) % (uint32_t)ntk) : 0;
+    auto tk = [&](int t) { return t + grot < ntk ? t + grot : t + grot - ntk; };
 
     // Tail rows: lane (i, g) of a compute wave loads 32 bytes of token
     // mrow0 + BM + i per stage, K 64 kh + 16 g .. +15 (its two MFMA steps).
@@ -460,114 +473,154 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     }
     const int wmu = __builtin_amdgcn_readfirstlane(wm);  // token half, wave-uniform
 
-    // ---- per-lane DMA state (fixed across stages) ------------------------------
-    // Stage t of a lane's weight piece starts at wp + 128 t (upper bytes) and,
-    // in full mode, at rp0/rp1 + 128 t (residual bytes in the first / second
-    // chunk the row's K range touches; the second serves stages >= tsw).  A
-    // piece lies inside [kb0, ke) while 128 t < wlim.  Token pieces likewise:
-    // xp + 128 t elements, inside while 128 t < xlim.
-    // weight instruction j: rows 8j .. 8j+7, lane -> row 8j + lane/8, slot lane%8
-    const uint8_t *wp[C::W_INSTR];
-    const uint8_t *rp0[C::W_INSTR], *rp1[C::W_INSTR];
-    int64_t wlog[C::W_INSTR];  // logical residual index of the piece at stage 0
-    int wlim[C::W_INSTR], tsw[C::W_INSTR];
-    bool rok0[C::W_INSTR], rok1[C::W_INSTR];
+    // ---- DMA sources ---------------------------------------------------------
+    // A wave that issues loads is paced by what each costs it to issue, so a
+    // load takes a scalar stage offset (buffer loads of the upper bytes and
+    // tokens) or one 64-bit add (residual bytes); stages cut by the K range's
+    // end and renewed residual pointers go through branches of their own.
+    // token instruction jj: rows 4j .. 4j+3 (j = X_INSTR issuer + jj), lane ->
+    // row 4j + lane/16, slot lane%16
+    constexpr int NP = C::W_INSTR, NX = C::X_INSTR;
     const bool issues = !SPEC || dma_wave;  // compute waves of a SPEC block keep no DMA state
+    const int xr0 = 4 * NX * issuer;
+    const int64_t xrow0 = issues && mrow0 + xr0 < mrow1 ? mrow0 + xr0 : mrow1 - 1;
+    const rsrc_t xr = make_rsrc(static_cast<const uint16_t *>(a.x) + xrow0 * a.k + kb0,
+                                ((mrow1 - xrow0) * a.k - kb0) * 2);
+    uint32_t xoff[NX];
 #pragma unroll
-    for (int jj = 0; jj < C::W_INSTR && issues; ++jj) {
-        const int j = issuer * C::W_INSTR + jj;
-        const int r = 8 * j + (lane >> 3);
-        int64_t nr = n0 + r;
-        nr = nr < a.n ? nr : a.n - 1;
-        const int wel = ((lane & 7) ^ swz8(r)) * 16;
-        const int64_t wl = (e * a.n + nr) * a.k;
-        wp[jj] = a.hi + wl + kb0 + wel;
-        wlim[jj] = (int)(ke - kb0 - wel);
-        wlog[jj] = wl + kb0 + wel;
-        rp0[jj] = rp1[jj] = a.res.pool;
-        tsw[jj] = 0;
-        rok0[jj] = rok1[jj] = false;
-        if (MODE == MODE_FULL && RANGE && ke > kb0) {
-            const RangeResidual rr = range_residual(a.res, wl + kb0, wl + ke);
-            rp0[jj] = a.res.pool + rr.delta0 + wlog[jj];
-            rp1[jj] = a.res.pool + rr.delta1 + wlog[jj];
-            rok0[jj] = rr.ok0;
-            rok1[jj] = rr.ok1;
-            const int64_t d = rr.bnd - wlog[jj];  // first stage at or past the chunk boundary
-            tsw[jj] = d <= 0 ? 0 : (int)((d + C::BK - 1) / C::BK);
-        }
+    for (int jj = 0; jj < NX; ++jj) {
+        const int r = 4 * jj + (lane >> 4);
+        xoff[jj] = (uint32_t)(r * a.k + ((lane & 15) ^ swz16(xr0 + r)) * 8) * 2u;
     }
-    // token instruction j: rows 4j .. 4j+3, lane -> row 4j + lane/16, slot lane%16
-    const uint16_t *xp[C::X_INSTR];
-    int xlim[C::X_INSTR];
+    auto issue_x = [&](int tr, int slot) {
+        lds_u8 *dst = lds + C::X_BASE + slot * C::X_SLOT + NX * 1024 * issuer;
+        if (tr < t_full) {
 #pragma unroll
-    for (int jj = 0; jj < C::X_INSTR && issues; ++jj) {
-        const int j = issuer * C::X_INSTR + jj;
-        const int r = 4 * j + (lane >> 4);
-        int64_t m = mrow0 + r;
-        m = m < mrow1 ? m : mrow1 - 1;
-        const int xel = ((lane & 15) ^ swz16(r)) * 8;
-        xp[jj] = static_cast<const uint16_t *>(a.x) + m * a.k + kb0 + xel;
-        xlim[jj] = (int)(ke - kb0 - xel);
-    }
-    // stages entirely inside the K range need no masks
-    const int64_t t_full = (ke - kb0) / C::BK;
-    // Iteration t stages K range tk(t).  With rows a multiple of 4 KiB apart,
-    // blocks walking their K ranges in step would all touch the same 128-byte
-    // column (address bits 7-11) at once; each group of four weight tiles
-    // starts at another stage instead.  Token tiles of one weight tile keep
-    // the same order, so they still meet in L2.  (MI355X, gate+up 28672 x
-    // 4096 in full mode: 0.78x the time at 32 tokens, 0.83x at 128, 0.91x at
-    // 256; the other hidden-4096 layers within 3%.)
-    const int64_t grot = a.rotate && ntk > 0 ? (uint32_t)(ntile >> 2) % (uint32_t)ntk : 0;
-    auto tk = [&](int64_t t) {
-        return t < ntk ? (t + grot < ntk ? t + grot : t + grot - ntk) : t;
-    };
-
-    // One DMA "unit": token instruction jj of stage t, or weight instruction jj
-    // of stage t (upper bytes and, in full mode, residual bytes).
-    auto issue_w1 = [&](int jj, int64_t t) {
-        uint8_t *st = smem + (int)(t % WS) * C::W_SLOT;
-        const int64_t tr = tk(t);
-        const bool masked = tr >= t_full;
-        const int64_t off = tr * C::BK;
-        const int j = issuer * C::W_INSTR + jj;
-        const bool ok = !masked || off < wlim[jj];
-        dma16<AUX>(ok ? (const void *)(wp[jj] + off) : (const void *)g_zero16, st + j * 1024);
-        if (MODE == MODE_FULL) {
-            const void *src = g_zero16;
-            if (RANGE) {
-                const bool second = tr >= tsw[jj];
-                const bool cok = second ? rok1[jj] : rok0[jj];
-                const uint8_t *base = second ? rp1[jj] : rp0[jj];
-                if (ok && cok)
-                    src = base + off;
-            } else {
-                const int64_t o = residual_offset(a.res, wlog[jj] + (ok ? off : 0));
-                if (ok && o >= 0)
-                    src = a.res.pool + o;
+            for (int jj = 0; jj < NX; ++jj)
+                buffer_load_lds(xr, dst + jj * 1024, 16, xoff[jj], tr * (C::BK * 2), 0, 0);
+        } else {
+            const int ln = lane_again();
+#pragma unroll
+            for (int jj = 0; jj < NX; ++jj) {
+                const int r = xr0 + 4 * jj + (ln >> 4);
+                const int kk = tr * C::BK + ((ln & 15) ^ swz16(r)) * 8;
+                const int64_t m = mrow0 + r;
+                const bool ok = m < mrow1 && kk < klen;
+                const uint16_t *src = static_cast<const uint16_t *>(a.x) + m * a.k + kb0 + kk;
+                dma16_at<AUX_CACHED>(ok ? (const void *)src : (const void *)g_zero16,
+                                     dst + jj * 1024);
             }
-            dma16<AUX>(src, st + C::W_BYTES + j * 1024);
+            rare_path_end();
         }
     };
-    auto issue_x1 = [&](int jj, int64_t t) {
-        uint8_t *st = smem + C::X_BASE + (int)(t % XS) * C::X_SLOT;
-        const int64_t tr = tk(t);
-        const bool masked = tr >= t_full;
-        const int64_t off = tr * C::BK;
-        const int j = issuer * C::X_INSTR + jj;
-        const bool ok = !masked || off < xlim[jj];
-        dma16(ok ? (const void *)(xp[jj] + off) : (const void *)g_zero16, st + j * 1024);
+    // weight instruction jj of a plane: rows 8j .. 8j+7 (j = W_INSTR issuer +
+    // jj), lane -> row 8j + lane/8, slot lane%8
+    auto w_row = [&](int ln, int jj, int &wel) {
+        const int r = 8 * (NP * issuer + jj) + (ln >> 3);
+        wel = ((ln & 7) ^ swz8(r)) * 16;
+        const int64_t nr = n0 + r;
+        return e * a.n + (nr < a.n ? nr : a.n - 1);
     };
-    auto issue_w = [&](int64_t t) {
+    const int wr0 = issues ? 8 * NP * issuer : 0;
+    const int64_t wrow0 = e * a.n + (n0 + wr0 < a.n ? n0 + wr0 : a.n - 1);
+    const rsrc_t wr = make_rsrc(a.hi + wrow0 * a.k + kb0, 0xFFFFFFFFll);
+    uint32_t woff[NP];
+    const uint8_t *wp[NP];  // full mode: residual pointer of the piece of K stage 0
+    int wev = tk(0);        // full mode: next stage whose residual pieces need new pointers
 #pragma unroll
-        for (int jj = 0; jj < C::W_INSTR; ++jj)
-            issue_w1(jj, t);
+    for (int jj = 0; jj < NP; ++jj) {
+        int wel;
+        const int64_t nr = w_row(lane, jj, wel);
+        woff[jj] = (uint32_t)((nr > wrow0 ? nr - wrow0 : 0) * a.k + wel);
+        wp[jj] = nullptr;
+    }
+    // Full mode: the residual pointers of stage tr's pieces, and the next stage
+    // in walk order at which any lane's piece leaves its chunk or passes the
+    // end of the K range (pieces without a source read zeros, stage by stage).
+    auto w_pointers = [&](int tr) {
+        const int ln = lane_again();
+        const int64_t off = (int64_t)tr * C::BK;
+        int lo_t = 0, hi_t = ntk;  // stages [lo_t, hi_t) keep these pointers
+#pragma unroll
+        for (int jj = 0; jj < NP; ++jj) {
+            int wel;
+            const int64_t nr = w_row(ln, jj, wel);
+            const int64_t l0 = nr * a.k + kb0 + wel;
+            const bool in = off + wel < klen;
+            const int64_t l = l0 + (in ? off : 0);
+            const int64_t o = residual_offset(a.res, l);
+            const bool ok = in && o >= 0;
+            const int64_t cb = (l >> a.res.log2c) << a.res.log2c;
+            const int64_t b0 = (cb - l0 + C::BK - 1) >> 7;
+            const int64_t b1 = (cb + (int64_t(1) << a.res.log2c) - l0 + C::BK - 1) >> 7;
+            const int t_in = (klen - wel + C::BK - 1) >> 7;
+            int t0 = b0 > 0 ? (int)b0 : 0;
+            int t1 = b1 < t_in ? (int)b1 : t_in;
+            wp[jj] = ok ? a.res.pool + (o - (in ? off : 0)) : g_zero16 - off;
+            t0 = ok ? t0 : tr;
+            t1 = ok ? t1 : tr + 1;
+            lo_t = t0 > lo_t ? t0 : lo_t;
+            hi_t = t1 < hi_t ? t1 : hi_t;
+        }
+        if (__all(lo_t <= 0 && hi_t >= ntk)) {
+            wev = -1;
+        } else {
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                const int u = __shfl_xor(hi_t, d, 64), v = __shfl_xor(lo_t, d, 64);
+                hi_t = u < hi_t ? u : hi_t;
+                lo_t = v > lo_t ? v : lo_t;
+            }
+            hi_t = __builtin_amdgcn_readfirstlane(hi_t);
+            lo_t = __builtin_amdgcn_readfirstlane(lo_t);
+            wev = hi_t < ntk ? hi_t : (lo_t > 0 ? 0 : -1);  // the walk may wrap to stage 0
+        }
+        rare_path_end();
     };
-    auto issue_x = [&](int64_t t) {
+    static_assert(C::BK == 128, "stage arithmetic of w_pointers");
+    auto issue_w = [&](int tr, int slot) {
+        lds_u8 *dst = lds + slot * C::W_SLOT + NP * 1024 * issuer;
+        if (tr < t_full) {
 #pragma unroll
-        for (int jj = 0; jj < C::X_INSTR; ++jj)
-            issue_x1(jj, t);
+            for (int jj = 0; jj < NP; ++jj)
+                buffer_load_lds(wr, dst + jj * 1024, 16, woff[jj], tr * C::BK, 0, AUX);
+        } else {
+            const int ln = lane_again();
+#pragma unroll
+            for (int jj = 0; jj < NP; ++jj) {
+                int wel;
+                const int64_t nr = w_row(ln, jj, wel);
+                const int kk = tr * C::BK + wel;
+                const uint8_t *src = a.hi + nr * a.k + kb0 + kk;
+                dma16_at<AUX>(kk < klen ? (const void *)src : (const void *)g_zero16,
+                              dst + jj * 1024);
+            }
+            rare_path_end();
+        }
+        if (MODE == MODE_FULL) {
+            if (tr == wev)
+                w_pointers(tr);
+#pragma unroll
+            for (int jj = 0; jj < NP; ++jj)
+                dma16_at<AUX>(wp[jj] + (int64_t)tr * C::BK, dst + C::W_BYTES + jj * 1024);
+        }
+    };
+    // Iteration t issues tokens of stage t + XS - 1, then weights of stage t +
+    // WS - 1, into the slots that stage t - 1 has left.
+    int iws = WS - 1, ixs = XS - 1;  // their slots
+    auto issue = [&](int t) {
+        if (t + XS - 1 < ntk)
+            issue_x(tk(t + XS - 1), ixs);
+        if (t + WS - 1 < ntk)
+            issue_w(tk(t + WS - 1), iws);
+        iws = iws + 1 < WS ? iws + 1 : 0;
+        ixs = ixs + 1 < XS ? ixs + 1 : 0;
+    };
+    auto wait = [&](int t) {  // tokens t and weights t have landed
+        if (t + WS - 1 <= ntk)
+            DPS_WAIT_VMCNT(C::OUTSTANDING);
+        else
+            DPS_WAIT_VMCNT(0);
     };
     f32x4 acc[4][C::MT];
 #pragma unroll
@@ -595,13 +648,16 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
 
     // one stage of matrix work on the slots of stage t (tail_c: std::true_type
     // in blocks with tail rows)
-    auto compute = [&](int64_t t, auto tail_c) {
+    int cws = 0, cxs = 0;  // slots of the stage being multiplied
+    auto compute = [&](int t, auto tail_c) {
         constexpr bool TL = decltype(tail_c)::value;
-        const uint8_t *st = smem + (int)(t % WS) * C::W_SLOT;
-        const uint8_t *xs = smem + C::X_BASE + (int)(t % XS) * C::X_SLOT;
+        const uint8_t *st = smem + cws * C::W_SLOT;
+        const uint8_t *xs = smem + C::X_BASE + cxs * C::X_SLOT;
+        cws = cws + 1 < WS ? cws + 1 : 0;
+        cxs = cxs + 1 < XS ? cxs + 1 : 0;
         u32x4 tx0 = {0u, 0u, 0u, 0u}, tx1 = {0u, 0u, 0u, 0u};
         if constexpr (TL) {
-            const int64_t off = tk(t) * C::BK;
+            const int off = tk(t) * C::BK;
             const bool ok = off < xtlim;
             const uint32_t msk = 0u - (uint32_t)ok;
             const uint16_t *p = xt + (ok ? off + xtk : 0);
@@ -618,10 +674,8 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
         }
         // without DMA waves, this wave issues its share of the next stages'
         // DMA here, after its fragment reads (their latency overlaps the issue)
-        if (!SPEC) {
-            issue_x(t + XS - 1);
-            issue_w(t + WS - 1);
-        }
+        if (!SPEC)
+            issue(t);
         half8 a0[4], a1[4];
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
@@ -654,43 +708,42 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
         }
     };
 
-    if (!SPEC || dma_wave) {
+    if (issues) {
         // prologue: the steady-state issue of iterations -(WS-1) .. -1, keeping
         // only stages >= 0, so the counter arithmetic holds from iteration 0
-#pragma unroll
+#pragma unroll 1
         for (int u = -(WS - 1); u < 0; ++u) {
-            if (u + XS - 1 >= 0)
-                issue_x(u + XS - 1);
-            if (u + WS - 1 >= 0)
-                issue_w(u + WS - 1);
+            if (u + XS - 1 >= 0 && u + XS - 1 < ntk)
+                issue_x(tk(u + XS - 1), u + XS - 1);
+            if (u + WS - 1 < ntk)
+                issue_w(tk(u + WS - 1), u + WS - 1);
         }
     }
     if (!SPEC) {
-        for (int64_t t = 0; t < ntk; ++t) {
-            DPS_WAIT_VMCNT(C::OUTSTANDING);  // tokens t and weights t have landed
+        for (int t = 0; t < ntk; ++t) {
+            wait(t);
             stage_barrier();
             compute(t, std::false_type{});
         }
     } else if (dma_wave) {
         // separate loops per role keep the DMA state out of the compute waves'
         // registers and the accumulators out of the DMA waves'
-        for (int64_t t = 0; t < ntk; ++t) {
-            DPS_WAIT_VMCNT(C::OUTSTANDING);
+        for (int t = 0; t < ntk; ++t) {
+            wait(t);
             stage_barrier();
-            issue_x(t + XS - 1);
-            issue_w(t + WS - 1);
+            issue(t);
         }
         DPS_WAIT_VMCNT(0);  // no DMA may still target this block's LDS
         __syncthreads();    // matches the compute waves' two barriers below
         __syncthreads();
         return;
     } else if (has_tail) {
-        for (int64_t t = 0; t < ntk; ++t) {
+        for (int t = 0; t < ntk; ++t) {
             stage_barrier();
             compute(t, std::integral_constant<bool, (TAIL > 0)>{});
         }
     } else {
-        for (int64_t t = 0; t < ntk; ++t) {
+        for (int t = 0; t < ntk; ++t) {
             stage_barrier();
             compute(t, std::false_type{});
         }
@@ -814,21 +867,12 @@ hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped
                               : dense_grid(nt * plan.splits * ((a.rows + BM - 1) / BM));
     const dim3 block(SPEC ? 768 : 512);
     constexpr int TL = SPEC && BM == 128 ? 16 : 0;
-    if (MODE == MODE_FULL && plan.range_addr) {
-        if (TL > 0 && grouped)
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC, AUX, TL>), grid,
-                               block, 0, stream, a);
-        else
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, true, SPEC, AUX>), grid,
-                               block, 0, stream, a);
-    } else {
-        if (TL > 0 && grouped)
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC, AUX, TL>), grid,
-                               block, 0, stream, a);
-        else
-            hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, false, SPEC, AUX>), grid,
-                               block, 0, stream, a);
-    }
+    if (TL > 0 && grouped)
+        hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, SPEC, AUX, TL>), grid, block, 0,
+                           stream, a);
+    else
+        hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, SPEC, AUX>), grid, block, 0,
+                           stream, a);
     return hipGetLastError();
 }
 

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
                 const bool ok = m < mrow1 && kk < klen;
                 const uint8_t *src =
                     static_cast<const uint8_t *>(a.x) + (m * a.k + kb0 + kk) * C::XB;
-                dma16_at(ok ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
+                dma16_at<AUX_CACHED>(ok ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
             }
             rare_path_end();
         }
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
         if (KIND == T_FULL) {
 #pragma unroll
             for (int jj = 0; jj < NW; ++jj)
-                dma16_at(wp[jj] + (int64_t)tr * C::BK, dst + jj * 1024);
+                dma16_at<AUX_CACHED>(wp[jj] + (int64_t)tr * C::BK, dst + jj * 1024);
         } else if (tr < t_full) {
 #pragma unroll
             for (int jj = 0; jj < NW; ++jj)
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
                 const int64_t nr = w_row(ln, jj, wel, lo);
                 const int kk = tr * C::BK + wel;
                 const uint8_t *src = a.hi + nr * a.k + kb0 + kk;
-                dma16_at(kk < klen ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
+                dma16_at<AUX_CACHED>(kk < klen ? (const void *)src : (const void *)g_zero16, dst + jj * 1024);
             }
             rare_path_end();
         }

@@ -107,10 +107,9 @@ __device__ __attribute__((aligned(16))) const uint8_t g_zero16[16] = {0};
 // weights of layers beyond kStreamBytes.
 enum { AUX_CACHED = 0, AUX_STREAM = 2 };
 
-template <int AUX = AUX_CACHED>
 __device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
 {
-    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, AUX);
+    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, 0);
 }
 
 // The same, 16 bytes per lane from `src` into the wave's 1 KiB at LDS address
@@ -121,12 +120,19 @@ __device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
 // business (vmcnt, in issue order).
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
+template <int AUX>
 __device__ __forceinline__ void dma16_at(const void *src, lds_u8 *lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"((uint32_t)(uintptr_t)lds), "v"(src)
-                 : "memory", "m0");
+    if (AUX == AUX_STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                     :
+                     : "s"((uint32_t)(uintptr_t)lds), "v"(src)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                     :
+                     : "s"((uint32_t)(uintptr_t)lds), "v"(src)
+                     : "memory", "m0");
 }
 
 // A raw buffer over [p, p + bytes): 48-bit base, byte count, data format 32
