@@ -338,7 +338,12 @@ __global__ __launch_bounds__(kThreads) void quant_rows_wave_kernel(const uint16_
     }
 }
 
-template <int VEC>
+// Bound by one round trip to memory (the partials come from other XCDs'
+// blocks).  S > 0: that many splits, every partial of an output in flight at
+// once and read past the caches; S = 0 any number, one after another.  MI355X,
+// decode passes with three reductions each: 32 tokens full E4M3 101.8 -> 99.5
+// us, 128 fast 99.2 -> 96.8 (cached loads: 98.7).
+template <int VEC, int S>
 __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *__restrict__ partial,
                                                                  int splits, int64_t rows,
                                                                  int64_t n,
@@ -350,10 +355,21 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *__
     for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < total; v += stride) {
         const int64_t i = v * VEC;
         if (VEC == 4) {
-            f32x4 acc = *reinterpret_cast<const f32x4 *>(partial + i);
-            for (int s = 1; s < splits; ++s) {
-                const f32x4 p = *reinterpret_cast<const f32x4 *>(partial + s * plane + i);
-                acc += p;
+            f32x4 acc;
+            if (S > 0) {
+                f32x4 p[S > 0 ? S : 1];
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+                    p[s] = __builtin_nontemporal_load(
+                        reinterpret_cast<const f32x4 *>(partial + s * plane + i));
+                acc = p[0];
+#pragma unroll
+                for (int s = 1; s < S; ++s)
+                    acc += p[s];
+            } else {
+                acc = *reinterpret_cast<const f32x4 *>(partial + i);
+                for (int s = 1; s < splits; ++s)
+                    acc += *reinterpret_cast<const f32x4 *>(partial + s * plane + i);
             }
             typedef _Float16 half4 __attribute__((ext_vector_type(4)));
             half4 h = {(_Float16)acc.x, (_Float16)acc.y, (_Float16)acc.z, (_Float16)acc.w};
@@ -448,16 +464,30 @@ hipError_t launch_quant_rows(const uint16_t *x, int64_t m, int64_t k, uint8_t *x
     }
 }
 
+template <int VEC, int S>
+hipError_t launch_reduce(const float *partial, int splits, int64_t rows, int64_t n, uint16_t *y,
+                         hipStream_t stream)
+{
+    hipLaunchKernelGGL((splitk_reduce_kernel<VEC, S>), dim3((unsigned)grid_for(rows * n / VEC)),
+                       dim3(kThreads), 0, stream, partial, splits, rows, n, y);
+    return hipGetLastError();
+}
+
 hipError_t launch_splitk_reduce(const float *partial, int splits, int64_t rows, int64_t n,
                                 uint16_t *y, hipStream_t stream)
 {
-    if (n % 4 == 0)
-        hipLaunchKernelGGL(splitk_reduce_kernel<4>, dim3((unsigned)grid_for(rows * n / 4)),
-                           dim3(kThreads), 0, stream, partial, splits, rows, n, y);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<1>, dim3((unsigned)grid_for(rows * n)),
-                           dim3(kThreads), 0, stream, partial, splits, rows, n, y);
-    return hipGetLastError();
+    if (n % 4 != 0)
+        return launch_reduce<1, 0>(partial, splits, rows, n, y, stream);
+    switch (splits) {
+    case 2: return launch_reduce<4, 2>(partial, splits, rows, n, y, stream);
+    case 3: return launch_reduce<4, 3>(partial, splits, rows, n, y, stream);
+    case 4: return launch_reduce<4, 4>(partial, splits, rows, n, y, stream);
+    case 5: return launch_reduce<4, 5>(partial, splits, rows, n, y, stream);
+    case 6: return launch_reduce<4, 6>(partial, splits, rows, n, y, stream);
+    case 7: return launch_reduce<4, 7>(partial, splits, rows, n, y, stream);
+    case 8: return launch_reduce<4, 8>(partial, splits, rows, n, y, stream);
+    default: return launch_reduce<4, 0>(partial, splits, rows, n, y, stream);
+    }
 }
 
 }  // namespace dps
