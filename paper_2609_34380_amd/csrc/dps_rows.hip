@@ -20,6 +20,11 @@
 //     direct-to-LDS loads, like the weights, so every load the kernel issues
 //     is counted by the same vector-memory counter and the ring's waits
 //     retire exactly what the stage about to be read needs;
+//     Calls of at most eight tokens stage eight, not sixteen, token rows: on a
+//     block of one row group a chunk's activations otherwise fill as many LDS
+//     bytes as its weights in full mode and twice as many in fast mode, and the
+//     fill is the bound (MI355X, 8 tokens: 4096 x 14336 17.2 -> 14.4 us fast,
+//     27.0 -> 25.2 full; the hidden-4096 pass in fast mode 56.6 -> 53.2);
 //   - at the end the eight slices are summed through LDS in wave order, so
 //     the result does not depend on timing, and written as FP16.
 // Weights are merged (full mode) or converted (fast mode) into FP16 words in
@@ -84,16 +89,16 @@ typedef const __attribute__((address_space(4))) int32_t *const_i32p;
 // XA bytes for its activation slice of one chunk: two where LDS allows
 // (the next chunk's slice then streams in while this one is read), else
 // one, refilled right after it has been read.
-template <int MODE, int NT, int G>
+template <int MODE, int XT, int G>
 struct RowsConfig {
     static constexpr int PLANES = MODE == MODE_FULL ? 2 : 1;
     static constexpr int SLOT = 16 * kRowsKC * PLANES;  // one stage
     static constexpr int WSMAX = MODE == MODE_FULL ? 4 : 8;
     static constexpr int WS = G + 2 < WSMAX ? G + 2 : WSMAX;
     static constexpr int NI = 2 * PLANES;  // DMA instructions per wave per stage
-    static constexpr int RED = 8 * G * NT * 1024;  // slice sums, reusing the ring
+    static constexpr int RED = 8 * G * 1024;  // slice sums, reusing the ring
     static constexpr int RING = WS * SLOT > RED ? WS * SLOT : RED;
-    static constexpr int XL = 4 * NT;              // activation instructions per wave per chunk
+    static constexpr int XL = XT / 4;              // activation instructions per wave per chunk
     static constexpr int XA = XL * 1024;           // activation area of one wave
     static constexpr int XB = RING + 2 * 8 * XA <= 160 * 1024 ? 2 : 1;
     static constexpr int LDS = RING + XB * 8 * XA;
@@ -101,13 +106,13 @@ struct RowsConfig {
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 
-// NT: 16-token tiles (tokens <= 16 NT); G: 16-row groups per block; RANGE:
+// XT: tokens staged, 16 or (at most eight tokens) 8; G: 16-row groups per block; RANGE:
 // residual chunks of >= 1 KiB, so that one row piece spans at most two
 // chunks (else a per-vector table lookup).
-template <int MODE, int ENC, int NT, int G, bool RANGE, int AUX>
+template <int MODE, int ENC, int XT, int G, bool RANGE, int AUX>
 __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
 {
-    using C = RowsConfig<MODE, NT, G>;
+    using C = RowsConfig<MODE, XT, G>;
     constexpr int SLOT = C::SLOT;
     constexpr int WS = C::WS;
     constexpr int NI = C::NI;
@@ -184,12 +189,14 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
             }
     };
 
-    // ---- activations of this wave's K slice for chunk step c: instruction q
-    // = (s2, h, nt) of lane (j, g) loads X[16 nt + j][kc(c) KC + 16 (8w + 4 s2
-    // + g) + 8 h .. +7] (token rows past m repeat row m-1; past K a valid
-    // address, the value is cleared when read) into 16-byte position `lane`
-    // of 1 KiB piece q of the wave's area, so each lane later reads back
-    // exactly its own 16 bytes.
+    // ---- activations of this wave's K slice for chunk step c, in 1 KiB pieces
+    // of the wave's area (token rows past m repeat row m-1; past K a valid
+    // address, the value is cleared when read).  XT = 16: piece (s2, h), lane
+    // (j, g) loads X[j][kc(c) KC + 16 (8w + 4 s2 + g) + 8 h .. +7] and reads
+    // its own 16 bytes back.  XT = 8 (at most eight tokens): piece s2 holds
+    // both halves, lane (j, g) loads token j % 8 and half j / 8, and lanes j
+    // and j + 8 read the same token, so a chunk's activations are half the
+    // bytes; the sums of tokens 8-15 are copies that nothing stores.
     constexpr int XL = C::XL;
     constexpr int XB = C::XB;
     // the wave's area for chunk c
@@ -198,25 +205,27 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
     };
     auto issue_x = [&](int64_t c, int64_t cbuf) {
         uint8_t *xa = xarea(cbuf);
+        int64_t tok = XT == 8 ? li & 7 : li;
+        tok = tok < a.m ? tok : a.m - 1;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            int64_t tok = 16 * nt + li;
-            tok = tok < a.m ? tok : a.m - 1;
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-                const int64_t kk = kc(c) * kRowsKC + 16 * (8 * wave + 4 * s2 + lg);
-                const int64_t kv = kk < a.k ? kk : 0;
+        for (int s2 = 0; s2 < 2; ++s2) {
+            const int64_t kk = kc(c) * kRowsKC + 16 * (8 * wave + 4 * s2 + lg);
+            const int64_t kv = kk < a.k ? kk : 0;
+            if (XT == 8) {
+                __builtin_amdgcn_global_load_lds(a.x + tok * a.k + kv + 8 * (li >> 3),
+                                                 DPS_ROWS_LDS(xa + s2 * 1024), 16, 0, 0);
+            } else {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
-                    __builtin_amdgcn_global_load_lds(
-                        a.x + tok * a.k + kv + 8 * h,
-                        DPS_ROWS_LDS(xa + ((s2 * 2 + h) * NT + nt) * 1024), 16, 0, 0);
+                    __builtin_amdgcn_global_load_lds(a.x + tok * a.k + kv + 8 * h,
+                                                     DPS_ROWS_LDS(xa + (s2 * 2 + h) * 1024), 16,
+                                                     0, 0);
             }
         }
     };
     // after the wait that retires chunk c's activation loads: registers from
     // the wave's area, with what lies past K cleared
-    u32x4 xr[2][2][NT];
+    u32x4 xr[2][2];
     auto read_x = [&](int64_t c) {
         const uint8_t *xa = xarea(c);
 #pragma unroll
@@ -224,22 +233,19 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
             const int64_t kk = kc(c) * kRowsKC + 16 * (8 * wave + 4 * s2 + lg);
             const uint32_t msk = 0u - (uint32_t)(kk < a.k);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    xr[s2][h][nt] = *reinterpret_cast<const u32x4 *>(
-                        xa + ((s2 * 2 + h) * NT + nt) * 1024 + lane * 16);
-                    xr[s2][h][nt] &= u32x4{msk, msk, msk, msk};
-                }
+            for (int h = 0; h < 2; ++h) {
+                const int at = XT == 8 ? s2 * 1024 + (16 * lg + 8 * h + (li & 7)) * 16
+                                       : (s2 * 2 + h) * 1024 + lane * 16;
+                xr[s2][h] = *reinterpret_cast<const u32x4 *>(xa + at);
+                xr[s2][h] &= u32x4{msk, msk, msk, msk};
+            }
         }
     };
 
-    f32x4 acc[G][NT];
+    f32x4 acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            acc[g][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // fragment offsets within a plane of a slot (fixed)
     int foff[2];
@@ -303,11 +309,8 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
                     lv = *reinterpret_cast<const u32x4 *>(slot + 16 * kRowsKC + foff[s2]);
                 const half8 w0 = weight8<MODE, ENC>(hv.x, hv.y, lv.x, lv.y);
                 const half8 w1 = weight8<MODE, ENC>(hv.z, hv.w, lv.z, lv.w);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    acc[g][nt] = mfma16x16x32(w0, as_half8(xr[s2][0][nt]), acc[g][nt]);
-                    acc[g][nt] = mfma16x16x32(w1, as_half8(xr[s2][1][nt]), acc[g][nt]);
-                }
+                acc[g] = mfma16x16x32(w0, as_half8(xr[s2][0]), acc[g]);
+                acc[g] = mfma16x16x32(w1, as_half8(xr[s2][1]), acc[g]);
             }
         }
     }
@@ -315,24 +318,20 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
     DPS_ROWS_WAIT_VMCNT(0);  // no DMA may still target the ring or the areas
     __syncthreads();         // every wave is done reading the ring
 
-    // ---- slice sums: wave w stores its tiles, then tile (g, nt) is summed
-    // over w = 0..7 in order by wave (g NT + nt) % 8.
+    // ---- slice sums: wave w stores its tiles, then the tile of group g is
+    // summed over w = 0..7 in order by wave g.
     f32x4 *red = reinterpret_cast<f32x4 *>(smem);
 #pragma unroll
     for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            red[((wave * G + g) * NT + nt) * 64 + lane] = acc[g][nt];
+        red[(wave * G + g) * 64 + lane] = acc[g];
     __syncthreads();
-    for (int tile = wave; tile < G * NT; tile += 8) {
-        const int g = tile / NT;
-        const int nt = tile % NT;
-        f32x4 s = red[((0 * G + g) * NT + nt) * 64 + lane];
+    for (int g = wave; g < G; g += 8) {
+        f32x4 s = red[g * 64 + lane];
 #pragma unroll
         for (int w = 1; w < 8; ++w)
-            s += red[((w * G + g) * NT + nt) * 64 + lane];
+            s += red[(w * G + g) * 64 + lane];
         // lane (j, q) holds rows 4q .. 4q+3 of the group for token j
-        const int64_t tok = 16 * nt + li;
+        const int64_t tok = li;
         const int64_t n0 = r0 + 16 * g + 4 * lg;
         if (tok < a.m && n0 < a.n) {
             uint16_t *yp = a.y + tok * a.n + n0;
@@ -350,48 +349,51 @@ __global__ __launch_bounds__(512) void rows_kernel(RowsArgs a)
 }
 
 // AUX: cache policy of the weight loads (kStreamBytes).
-template <int MODE, int ENC, int NT, int G, int AUX>
+template <int MODE, int ENC, int XT, int G, int AUX>
 hipError_t launch_aux(const RowsArgs &a, bool range, hipStream_t stream)
 {
     const dim3 grid((unsigned)((a.n + 16 * G - 1) / (16 * G)));
     if (MODE == MODE_FULL && !range)
-        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, false, AUX>), grid, dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((rows_kernel<MODE, ENC, XT, G, false, AUX>), grid, dim3(512), 0, stream,
+                           a);
     else
-        hipLaunchKernelGGL((rows_kernel<MODE, ENC, NT, G, true, AUX>), grid, dim3(512), 0, stream, a);
+        hipLaunchKernelGGL((rows_kernel<MODE, ENC, XT, G, true, AUX>), grid, dim3(512), 0, stream,
+                           a);
     return hipGetLastError();
 }
 
-template <int MODE, int ENC, int NT, int G>
-hipError_t launch_g(const RowsArgs &a, bool range, hipStream_t stream)
+template <int MODE, int ENC, int XT, int G>
+hipError_t launch_xt(const RowsArgs &a, bool range, hipStream_t stream)
 {
     return a.n * a.k * (MODE == MODE_FULL ? 2 : 1) >= kStreamBytes
-               ? launch_aux<MODE, ENC, NT, G, 2>(a, range, stream)
-               : launch_aux<MODE, ENC, NT, G, 0>(a, range, stream);
+               ? launch_aux<MODE, ENC, XT, G, 2>(a, range, stream)
+               : launch_aux<MODE, ENC, XT, G, 0>(a, range, stream);
 }
 
-template <int MODE, int ENC, int NT>
-hipError_t launch_nt(const RowsArgs &a, int groups, bool range, hipStream_t stream)
+template <int MODE, int ENC, int G>
+hipError_t launch_g(const RowsArgs &a, bool range, hipStream_t stream)
 {
-    switch (groups) {
-    case 1: return launch_g<MODE, ENC, NT, 1>(a, range, stream);
-    case 2: return launch_g<MODE, ENC, NT, 2>(a, range, stream);
-    case 3: return launch_g<MODE, ENC, NT, 3>(a, range, stream);
-    case 4: return launch_g<MODE, ENC, NT, 4>(a, range, stream);
-    case 5: return launch_g<MODE, ENC, NT, 5>(a, range, stream);
-    case 6: return launch_g<MODE, ENC, NT, 6>(a, range, stream);
-    case 7: return launch_g<MODE, ENC, NT, 7>(a, range, stream);
-    case 8: return launch_g<MODE, ENC, NT, 8>(a, range, stream);
-    default: return hipErrorInvalidValue;
-    }
+    return a.m <= 8 ? launch_xt<MODE, ENC, 8, G>(a, range, stream)
+                    : launch_xt<MODE, ENC, 16, G>(a, range, stream);
 }
 
 // One 16-token tile: with two (17-32 tokens) every block re-reads twice the
-// activations, and on MI355X the hidden-4096 layers ran 5-70% slower than on
-// the wide-row GEMM's 32-token tile.
+// activations, and on MI355X the hidden-4096 layers ran 0-80% slower than on
+// the wide-row GEMM's 32-token tile with its split-K reduction.
 template <int MODE, int ENC>
 hipError_t launch_mode(const RowsArgs &a, int groups, bool range, hipStream_t stream)
 {
-    return launch_nt<MODE, ENC, 1>(a, groups, range, stream);
+    switch (groups) {
+    case 1: return launch_g<MODE, ENC, 1>(a, range, stream);
+    case 2: return launch_g<MODE, ENC, 2>(a, range, stream);
+    case 3: return launch_g<MODE, ENC, 3>(a, range, stream);
+    case 4: return launch_g<MODE, ENC, 4>(a, range, stream);
+    case 5: return launch_g<MODE, ENC, 5>(a, range, stream);
+    case 6: return launch_g<MODE, ENC, 6>(a, range, stream);
+    case 7: return launch_g<MODE, ENC, 7>(a, range, stream);
+    case 8: return launch_g<MODE, ENC, 8>(a, range, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
