@@ -298,6 +298,7 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         p.ksplit = round_up(cdiv(k, s), g5 ? 64 : 128);
         p.splits = (int)cdiv(k, p.ksplit);
     }
+    p.cus = cu_count;
     p.range_addr = mode == MODE_FULL && p.ksplit <= (int64_t(1) << log2c);
     p.ws_partial = p.splits > 1 ? align256((int64_t)p.splits * rows * n * 4) : 0;
     return p;

@@ -927,6 +927,7 @@ hipError_t launch_gemm_f16(const LinearProblem &p, const LinearPlan &plan, float
     a.y = p.y;
     a.partial = partial;
     a.scale = nullptr;
+    a.cus = plan.cus;
     a.rotate = p.k % 4096 == 0;
     const bool grouped = p.offsets != nullptr;
     if (plan.variant == GEMM_G5_256x256)
@@ -956,6 +957,7 @@ hipError_t launch_gemm_fp8(int enc, const uint8_t *xq, const float *scale, const
     a.y = y;
     a.partial = partial;
     a.scale = scale;
+    a.cus = plan.cus;
     a.rotate = 0;
     if (plan.variant == GEMM_G3_256x256)
         return offsets ? hipErrorInvalidValue : launch_gemm256_fp8(enc, a, stream);

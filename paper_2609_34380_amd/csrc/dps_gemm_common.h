@@ -21,6 +21,7 @@ struct GemmArgs {
     uint16_t *y;
     float *partial;
     const float *scale;
+    int cus;     // compute units of the device (the 256 x 256 tile's grid)
     int rotate;  // wide-row GEMM: start each block's K walk by weight tile (see gemm4)
 };
 

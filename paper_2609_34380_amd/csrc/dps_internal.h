@@ -86,6 +86,7 @@ struct LinearPlan {
     int variant;       // kernel-family specific tile variant
     int splits;        // K is cut into `splits` ranges of `ksplit` elements
     int64_t ksplit;
+    int cus;           // compute units of the device
     bool range_addr;   // each row's residual range in a split spans <= 2 chunks
     size_t ws_partial; // fp32 split-K partials, bytes
     size_t ws_quant;   // E4M3 activations + row scales, bytes
