@@ -79,10 +79,11 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     static_assert(TAIL == 0 || (TAIL == 16 && DW && BM_ == 128 && WM == 2 && C::NT == 4),
                   "tail rows: the 256 x 128 tile with DMA waves");
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
+    lds_u8 *const lds = (lds_u8 *)smem;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15;
     const int lg = lane >> 4;
     // DW: four more waves (one per SIMD) only issue the direct-to-LDS loads
@@ -108,25 +109,27 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         // x is given the contiguous tile range [x * per_xcd, (x+1) * per_xcd),
         // walked with the token tile fastest.  Blocks sharing a weight tile
         // then run together on one XCD and fetch it into that XCD's L2 once.
-        const int64_t mtiles = (a.rows + BM_ - 1) / BM_;
-        const int64_t ntiles = (a.n + BN_ - 1) / BN_;
-        const int64_t total = mtiles * ntiles * a.splits;
-        const int64_t per_xcd = (total + 7) / 8;
-        const int64_t lin = blockIdx.x;
-        const int64_t t0 = (lin % 8) * per_xcd + lin / 8;
+        const uint32_t mtiles = (uint32_t)((a.rows + BM_ - 1) / BM_);
+        const uint32_t ntiles = (uint32_t)((a.n + BN_ - 1) / BN_);
+        const uint32_t total = mtiles * ntiles * (uint32_t)a.splits;
+        const uint32_t per_xcd = (total + 7) / 8;
+        const uint32_t t0 = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
         if (t0 >= total)
             return;
         ntile = (int)((t0 / mtiles) % ntiles);
         s = (int)(t0 / (mtiles * ntiles));
         e = 0;
-        mrow0 = (t0 % mtiles) * BM_;
+        mrow0 = (int64_t)(t0 % mtiles) * BM_;
         mrow1 = mrow0 + BM_ < a.rows ? mrow0 + BM_ : a.rows;
         mtail1 = mrow1;
     }
     const int64_t n0 = (int64_t)ntile * BN_;
     const int64_t kb0 = (int64_t)s * a.ksplit;
     const int64_t ke = kb0 + a.ksplit < a.k ? kb0 + a.ksplit : a.k;
-    const int64_t ntk = ke > kb0 ? (ke - kb0 + C::BK - 1) / C::BK : 0;
+    const int klen = (int)(ke - kb0);
+    const int ntk = (klen + C::BK - 1) / C::BK;
+    // stages entirely inside the K range, whose loads take 32-bit row offsets
+    const int t_full = a.k <= kMaxOffsetK ? klen / C::BK : 0;
 
     // Tail rows: lane (i, g) of a compute wave reads bytes 16g .. 16g+15 and
     // 64+16g .. 64+16g+15 of each stage of token mrow0 + BM_ + i (the slice
@@ -142,55 +145,70 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         xt += m * a.k + kb0;
     }
 
-    // ---- per-lane DMA sources (fixed across stages) ------------------------------
-    // instruction j covers LDS bytes j*1024 .. +1023 of its operand tile:
-    // rows 8j .. 8j+7, lane -> row 8j + lane/8, slot lane%8
-    const uint8_t *wsrc[C::W_INSTR];
-    int wel[C::W_INSTR];  // K offset of this lane's chunk within the stage
+    // ---- DMA sources: buffer loads with a scalar stage offset ---------------------
+    // instruction jj of an issuing wave covers rows 8j .. 8j+7 of its operand
+    // tile (j = its instructions per stage times iss, plus jj): lane -> row
+    // 8j + lane/8, slot lane%8.  Rows past the operand's end lie beyond its
+    // resource; what they leave in LDS is never stored.
+    constexpr int NW = C::W_INSTR, NX = C::X_INSTR;
+    const int wr0 = issues ? 8 * NW * iss : 0, xr0 = issues ? 8 * NX * iss : 0;
+    const int64_t wrow0 = n0 + wr0 < a.n ? n0 + wr0 : a.n - 1;
+    const int64_t xrow0 = mrow0 + xr0 < mrow1 ? mrow0 + xr0 : mrow1 - 1;
+    const rsrc_t wr = make_rsrc(a.hi + (e * a.n + wrow0) * a.k + kb0, (a.n - wrow0) * a.k - kb0);
+    const rsrc_t xr = make_rsrc(static_cast<const uint8_t *>(a.x) + xrow0 * a.k + kb0,
+                                (mrow1 - xrow0) * a.k - kb0);
+    const uint32_t step = (uint32_t)(8 * a.k);  // eight rows on
+    uint32_t off[2];  // instructions of even and odd j
 #pragma unroll
-    for (int jj = 0; jj < C::W_INSTR && issues; ++jj) {
-        const int j = iss * C::W_INSTR + jj;
-        const int r = 8 * j + (lane >> 3);
-        int64_t nr = n0 + r;
-        nr = nr < a.n ? nr : a.n - 1;
-        wsrc[jj] = a.hi + (e * a.n + nr) * a.k;
-        wel[jj] = ((lane & 7) ^ g3_swz(r)) * 16;
-    }
-    const uint8_t *xsrc[C::X_INSTR];
-    int xel[C::X_INSTR];
+    for (int par = 0; par < 2; ++par)
+        off[par] = (uint32_t)((lane >> 3) * a.k +
+                              ((lane & 7) ^ g3_swz(8 * par + (lane >> 3))) * 16);
+    static_assert(NW % 2 == 0 && NX % 2 == 0, "instruction parity");
+    auto issue_op = [&](auto n_c, const rsrc_t &r, const uint8_t *base, int64_t row0, int64_t row1,
+                        int tr, lds_u8 *dst) {
+        constexpr int N = decltype(n_c)::value;
+        if (tr < t_full) {
 #pragma unroll
-    for (int jj = 0; jj < C::X_INSTR && issues; ++jj) {
-        const int j = iss * C::X_INSTR + jj;
-        const int r = 8 * j + (lane >> 3);
-        int64_t m = mrow0 + r;
-        m = m < mrow1 ? m : mrow1 - 1;
-        xsrc[jj] = static_cast<const uint8_t *>(a.x) + m * a.k;
-        xel[jj] = ((lane & 7) ^ g3_swz(r)) * 16;
-    }
-
-    auto issue_w = [&](int64_t t) {
-        uint8_t *st = smem + (int)(t % WS) * C::W_BYTES;
-        const bool live = t < ntk;
-        const int64_t kt = kb0 + t * C::BK;
+            for (int jj = 0; jj < N; ++jj)
+                buffer_load_lds(r, dst + jj * 1024, 16, off[jj & 1] + jj * step, tr * C::BK, 0, 0);
+        } else {
+            const int ln = lane_again();
 #pragma unroll
-        for (int jj = 0; jj < C::W_INSTR; ++jj) {
-            const int j = iss * C::W_INSTR + jj;
-            const int64_t kk = kt + wel[jj];
-            const bool ok = live && kk < ke;
-            dma16(ok ? (const void *)(wsrc[jj] + kk) : (const void *)g_zero16, st + j * 1024);
+            for (int jj = 0; jj < N; ++jj) {
+                const int rr = 8 * jj + (ln >> 3);
+                const int kk = tr * C::BK + ((ln & 7) ^ g3_swz(rr)) * 16;
+                const bool ok = row0 + rr < row1 && kk < klen;
+                const uint8_t *src = base + (row0 + rr) * a.k + kb0 + kk;
+                dma16_at<AUX_CACHED>(ok ? (const void *)src : (const void *)g_zero16,
+                                     dst + jj * 1024);
+            }
+            rare_path_end();
         }
     };
-    auto issue_x = [&](int64_t t) {
-        uint8_t *st = smem + C::X_BASE + (int)(t % XS) * C::X_BYTES;
-        const bool live = t < ntk;
-        const int64_t kt = kb0 + t * C::BK;
-#pragma unroll
-        for (int jj = 0; jj < C::X_INSTR; ++jj) {
-            const int j = iss * C::X_INSTR + jj;
-            const int64_t kk = kt + xel[jj];
-            const bool ok = live && kk < ke;
-            dma16(ok ? (const void *)(xsrc[jj] + kk) : (const void *)g_zero16, st + j * 1024);
-        }
+    auto issue_w = [&](int t, int slot) {
+        if (t < ntk)
+            issue_op(std::integral_constant<int, NW>{}, wr, a.hi + e * a.n * a.k, n0 + wr0, a.n, t,
+                     lds + slot * C::W_BYTES + NW * 1024 * iss);
+    };
+    auto issue_x = [&](int t, int slot) {
+        if (t < ntk)
+            issue_op(std::integral_constant<int, NX>{}, xr, static_cast<const uint8_t *>(a.x),
+                     mrow0 + xr0, mrow1, t, lds + C::X_BASE + slot * C::X_BYTES + NX * 1024 * iss);
+    };
+    // Iteration t issues tokens of stage t + XS - 1, then weights of stage t +
+    // WS - 1, into the slots that stage t - 1 has left.
+    int iws = WS - 1, ixs = XS - 1;  // their slots
+    auto issue = [&](int t) {
+        issue_x(t + XS - 1, ixs);
+        issue_w(t + WS - 1, iws);
+        iws = iws + 1 < WS ? iws + 1 : 0;
+        ixs = ixs + 1 < XS ? ixs + 1 : 0;
+    };
+    auto wait = [&](int t) {  // tokens t and weights t have landed
+        if (t + WS - 1 <= ntk)
+            DPS_WAIT_VMCNT(C::OUTSTANDING);
+        else
+            DPS_WAIT_VMCNT(0);
     };
 
     const int wn = wave % WN;
@@ -204,21 +222,19 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
 
     // prologue: the steady-state issue of iterations -(WS-1) .. -1, keeping
     // only stages >= 0
-#pragma unroll
+#pragma unroll 1
     for (int u = -(WS - 1); u < 0 && issues; ++u) {
         if (u + XS - 1 >= 0)
-            issue_x(u + XS - 1);
-        if (u + WS - 1 >= 0)
-            issue_w(u + WS - 1);
+            issue_x(u + XS - 1, u + XS - 1);
+        issue_w(u + WS - 1, u + WS - 1);
     }
     if (DW && dma_wave) {
-        // the DMA waves' own loop keeps their source pointers out of the
-        // compute waves' registers (and the accumulators out of theirs)
-        for (int64_t t = 0; t < ntk; ++t) {
-            DPS_WAIT_VMCNT(C::OUTSTANDING);  // tokens t and weights t have landed
+        // the DMA waves' own loop keeps their state out of the compute waves'
+        // registers (and the accumulators out of theirs)
+        for (int t = 0; t < ntk; ++t) {
+            wait(t);
             stage_barrier();
-            issue_x(t + XS - 1);
-            issue_w(t + WS - 1);
+            issue(t);
         }
         DPS_WAIT_VMCNT(0);  // no DMA may still target this block's LDS when it exits
         return;
@@ -227,26 +243,27 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     const int wmu = __builtin_amdgcn_readfirstlane(wm);  // token half, wave-uniform
     // one stage of a compute wave, which without DW also issues its share of
     // the DMA (tail_c: std::true_type in blocks with tail rows)
-    auto stage = [&](int64_t t, auto tail_c) {
+    int cws = 0, cxs = 0;  // slots of the stage being multiplied
+    auto stage = [&](int t, auto tail_c) {
         constexpr bool TL = decltype(tail_c)::value;
         if (!DW)
-            DPS_WAIT_VMCNT(C::OUTSTANDING);  // tokens t and weights t have landed
+            wait(t);
         stage_barrier();
-        if (!DW) {
-            issue_x(t + XS - 1);
-            issue_w(t + WS - 1);
-        }
+        if (!DW)
+            issue(t);
         u32x4 tp = {0u, 0u, 0u, 0u}, tq = {0u, 0u, 0u, 0u};
         if constexpr (TL) {
-            const int64_t off = t * C::BK + 16 * lg;
-            const bool ok = kb0 + off < ke;
+            const int toff = t * C::BK + 16 * lg;
+            const bool ok = toff < klen;
             const uint32_t msk = 0u - (uint32_t)ok;
-            const uint8_t *pp = xt + (ok ? off : 0);
+            const uint8_t *pp = xt + (ok ? toff : 0);
             tp = load16(pp) & u32x4{msk, msk, msk, msk};
             tq = load16(pp + (ok ? 64 : 0)) & u32x4{msk, msk, msk, msk};
         }
-        const uint8_t *st = smem + (int)(t % WS) * C::W_BYTES;
-        const uint8_t *xs = smem + C::X_BASE + (int)(t % XS) * C::X_BYTES;
+        const uint8_t *st = smem + cws * C::W_BYTES;
+        const uint8_t *xs = smem + C::X_BASE + cxs * C::X_BYTES;
+        cws = cws + 1 < WS ? cws + 1 : 0;
+        cxs = cxs + 1 < XS ? cxs + 1 : 0;
         i32x8 av[C::NT];
 #pragma unroll
         for (int nt = 0; nt < C::NT; ++nt) {
@@ -284,10 +301,10 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         }
     };
     if (has_tail) {
-        for (int64_t t = 0; t < ntk; ++t)
+        for (int t = 0; t < ntk; ++t)
             stage(t, std::integral_constant<bool, (TAIL > 0)>{});
     } else {
-        for (int64_t t = 0; t < ntk; ++t)
+        for (int t = 0; t < ntk; ++t)
             stage(t, std::false_type{});
     }
     DPS_WAIT_VMCNT(0);  // no DMA may still target this block's LDS when it exits

@@ -121,19 +121,23 @@ __device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
 // business (vmcnt, in issue order).
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
+// M0 is put back, since the compiler keeps values of its own there.
 template <int AUX>
 __device__ __forceinline__ void dma16_at(const void *src, lds_u8 *lds)
 {
+    uint32_t m0;
     if (AUX == AUX_STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-                     :
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, off nt\n\ts_mov_b32 m0, %0"
+                     : "=&s"(m0)
                      : "s"((uint32_t)(uintptr_t)lds), "v"(src)
-                     : "memory", "m0");
+                     : "memory");
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                     :
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+                     : "=&s"(m0)
                      : "s"((uint32_t)(uintptr_t)lds), "v"(src)
-                     : "memory", "m0");
+                     : "memory");
 }
 
 // A raw buffer over [p, p + bytes): 48-bit base, byte count, data format 32
