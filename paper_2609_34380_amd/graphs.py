@@ -32,6 +32,10 @@ class ModeGraphs:
         self.graphs = {}
 
     def capture(self):
+        # The eager passes read what the caller has just enqueued (inputs, weight
+        # splits) and write memory that its allocator may have taken from
+        # tensors still in use there: they start after it.
+        self.stream.wait_stream(torch.cuda.current_stream(self.stream.device))
         with torch.cuda.stream(self.stream):
             for m in self.batch_sizes:
                 for mode in self.MODES:

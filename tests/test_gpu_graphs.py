@@ -81,3 +81,23 @@ def test_graph_pair_replays_match_eager():
                              "replay %d m=%d mode=%d layer %d" % (it, m, mode, li))
     with pytest.raises(KeyError):
         mg.replay(3, dps.MODE_FAST)
+
+
+def test_capture_starts_after_the_callers_work():
+    """The eager passes of capture() run on another stream than the caller's:
+    what the caller has enqueued before (here a fill behind a long kernel) is
+    done when they read it."""
+    x = torch.zeros(1 << 16, dtype=torch.float16, device=DEV)
+    y = torch.empty_like(x)
+    seen = []
+
+    def step(m, mode):
+        y.copy_(x)
+        if not torch.cuda.is_current_stream_capturing():
+            seen.append(y.clone())
+
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)
+    x.fill_(1.0)
+    graphs.ModeGraphs(step, (1,)).capture()
+    assert len(seen) == 2 and all(bool((s == 1.0).all()) for s in seen)
