@@ -143,7 +143,7 @@ dps_status check_weight(const dps_weight *w, int mode)
 namespace dps {
 
 LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_t k,
-                       int64_t experts, int log2c, int cu_count, bool grouped)
+                       int64_t experts, int log2c, int cu_count, bool grouped, bool part_filled)
 {
     LinearPlan p;
     memset(&p, 0, sizeof(p));
@@ -283,7 +283,7 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
             ranges = ranges < 1 ? 1 : (ranges > 4 ? 4 : ranges);
             if (rows >= 512 && (t5 >= cus || (k >= 8192 && 2 * t5 >= cus)))
                 p.variant = GEMM_G5_256x256;
-            else if (t5 < cus && t4 > cus && t4 % cus != 0 && 2 * t5 * ranges > cus)
+            else if (part_filled && t5 < cus && t4 > cus && t4 % cus != 0 && 2 * t5 * ranges > cus)
                 p.variant = GEMM_G5_256x256;
         }
         const bool g5 = p.variant == GEMM_G5_256x256;
@@ -488,11 +488,17 @@ dps_status run_linear(int mode, uint32_t flags, const uint16_t *x, const int32_t
                       int64_t rows, const dps_weight *w, uint16_t *y, void *ws, size_t ws_bytes,
                       hipStream_t stream, bool grouped)
 {
-    const dps::LinearPlan plan =
-        dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts,
-                         mode == DPS_MODE_FULL ? w->res.log2_chunk : 30, current_cu_count(),
-                         grouped);
-    const size_t need = plan.ws_partial + plan.ws_quant;
+    const int log2c = mode == DPS_MODE_FULL ? w->res.log2_chunk : 30;
+    dps::LinearPlan plan = dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts, log2c,
+                                            current_cu_count(), grouped);
+    size_t need = plan.ws_partial + plan.ws_quant;
+    if (need > 0 && (ws == nullptr || ws_bytes < need)) {
+        // A workspace sized for longer calls, whose plans split no K, can be
+        // too small for a part-filled grid's K ranges: the 128-row tile serves.
+        plan = dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts, log2c,
+                                current_cu_count(), grouped, false);
+        need = plan.ws_partial + plan.ws_quant;
+    }
     if (need > 0) {
         REQUIRE(ws != nullptr && ws_bytes >= need, DPS_ERR_WORKSPACE,
                 "workspace is smaller than dps_workspace_bytes()");

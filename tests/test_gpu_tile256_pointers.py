@@ -70,3 +70,20 @@ def test_part_filled_grids_take_the_tile(m, n, k, splits, mode):
     ref = oracle.linear_rows(oracle.FAST if mode == dps.MODE_FAST else oracle.FULL, u16(x), rows,
                              nst.hi_ref, nst.res_ref if mode == dps.MODE_FULL else None)
     assert_close(y[torch.from_numpy(rows).to(DEV)], ref)
+
+
+def test_small_workspace_still_runs():
+    """A call whose K ranges need a workspace runs with a smaller one, on the
+    128-row tile; a call that cannot do without stays refused."""
+    m, n, k = 700, 8190, 4112
+    ws = torch.empty(256, dtype=torch.uint8, device=DEV)
+    assert dps.workspace_bytes(dps.MODE_FAST, dps.ACT_FP16, m, n, k, 1) > ws.numel()
+    nst = Nested(workloads.weight_fp16(n, k, seed=83), 14, slot_seed=3)
+    x = workloads.activations_fp16(m, k, seed=84)
+    y = dps.linear(x.to(DEV), nst.nw, dps.MODE_FAST, workspace=ws)
+    rows = np.concatenate([np.arange(0, m, 37), [m - 1]])
+    ref = oracle.linear_rows(oracle.FAST, u16(x), rows, nst.hi_ref, None)
+    assert_close(y[torch.from_numpy(rows).to(DEV)], ref)
+    assert dps.workspace_bytes(dps.MODE_FAST, dps.ACT_FP16, 40, n, k, 1) > ws.numel()
+    with pytest.raises(dps.DpsError):
+        dps.linear(x[:40].contiguous().to(DEV), nst.nw, dps.MODE_FAST, workspace=ws)
