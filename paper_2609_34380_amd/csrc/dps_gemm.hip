@@ -494,7 +494,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     // A wave that issues loads is paced by what each costs it to issue, so a
     // load takes a scalar stage offset (buffer loads of the upper bytes and
     // tokens) or one 64-bit add (residual bytes); stages cut by the K range's
-    // end and renewed residual pointers go through branches of their own.
+    // end and rows that cross residual chunks go through branches of their own.
     // token instruction jj: rows 4j .. 4j+3 (j = X_INSTR issuer + jj), lane ->
     // row 4j + lane/16, slot lane%16
     constexpr int NP = C::W_INSTR, NX = C::X_INSTR;
@@ -542,60 +542,134 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     const int64_t wrow0 = e * a.n + (n0 + wr0 < a.n ? n0 + wr0 : a.n - 1);
     const rsrc_t wr = make_rsrc(a.hi + wrow0 * a.k + kb0, 0xFFFFFFFFll);
     uint32_t woff[NP];
-    const uint8_t *wp[NP];  // full mode: residual pointer of the piece of K stage 0
-    int wev = tk(0);        // full mode: next stage whose residual pieces need new pointers
 #pragma unroll
     for (int jj = 0; jj < NP; ++jj) {
         int wel;
         const int64_t nr = w_row(lane, jj, wel);
         woff[jj] = (uint32_t)((nr > wrow0 ? nr - wrow0 : 0) * a.k + wel);
-        wp[jj] = nullptr;
     }
-    // Full mode: the residual pointers of stage tr's pieces, and the next stage
-    // in walk order at which any lane's piece leaves its chunk or passes the
-    // end of the K range (pieces without a source read zeros, stage by stage).
-    auto w_pointers = [&](int tr) {
-        const int ln = lane_again();
-        const int64_t off = (int64_t)tr * C::BK;
-        int lo_t = 0, hi_t = ntk;  // stages [lo_t, hi_t) keep these pointers
+    // Full mode: the residual piece of instruction jj and stage t is at wp[jj] +
+    // 128 t.
+    //   W_ONE    for the whole K range
+    //   W_TWO    before stage wb[jj]; from there on rd[jj] chunks further (rows of
+    //            at most two chunks: K ranges no longer than a chunk)
+    //   W_RENEW  in the stages [w_lo, w_hi); looked up anew beyond them (shorter
+    //            chunks; slots outside the pool, whose pieces read zeros, stage
+    //            by stage)
+    // A lookup waits for the slot table and with it for every load this wave
+    // has in flight, so the first one comes before all loads and rows that
+    // cross chunks must not cost one per crossing (MI355X, 4096 x 4112 in 16
+    // KiB chunks, 64 tokens: 26.0 us with lookups at the crossings, 16.2 with
+    // both chunks' slots read once).
+    enum { W_ONE, W_TWO, W_RENEW };
+    const uint8_t *wp[NP];
+    int32_t rd[NP];
+    int wb[NP];
+    int wmode = W_RENEW, w_lo = 1, w_hi = 0;
+    const uint32_t cmask = (1u << a.res.log2c) - 1;
+    auto w_first = [&]() __attribute__((always_inline)) {
+        const int tr = tk(0);
+        int64_t l0[NP];
+        int32_t s0[NP], s1[NP];
+        bool ok = true, two = false;
+        auto slot_of = [&](int64_t c) {
+            const bool in = c < a.res.n_chunks;
+            ok &= in;
+            return a.res.slots[in ? c : 0];
+        };
 #pragma unroll
         for (int jj = 0; jj < NP; ++jj) {
             int wel;
-            const int64_t nr = w_row(ln, jj, wel);
-            const int64_t l0 = nr * a.k + kb0 + wel;
+            l0[jj] = w_row(lane, jj, wel) * a.k + kb0;  // of a piece past a short K range: the row's
+            l0[jj] += wel < klen ? wel : 0;
+            const int b = (int)((cmask - ((uint32_t)l0[jj] & cmask) + C::BK) >> 7);
+            const bool second = (int64_t)b * C::BK + wel < klen;
+            wb[jj] = second ? b : ntk;
+            two |= second;
+            s0[jj] = s1[jj] = slot_of(l0[jj] >> a.res.log2c);
+        }
+        const bool any_two = __any(two);
+        if (any_two) {
+#pragma unroll
+            for (int jj = 0; jj < NP; ++jj)
+                if (wb[jj] < ntk)
+                    s1[jj] = slot_of((l0[jj] >> a.res.log2c) + 1);
+        }
+        w_hi = ntk;
+#pragma unroll
+        for (int jj = 0; jj < NP; ++jj) {
+            ok &= s0[jj] >= 0 && s0[jj] < a.res.n_pool_slots && s1[jj] >= 0 &&
+                  s1[jj] < a.res.n_pool_slots;
+            rd[jj] = s1[jj] - s0[jj] - 1;
+            const bool next = wb[jj] <= tr;
+            const int64_t s = s0[jj] + (next ? (int64_t)rd[jj] : 0);
+            wp[jj] = a.res.pool + ((s << a.res.log2c) + ((uint32_t)l0[jj] & cmask));
+            w_hi = !next && wb[jj] < w_hi ? wb[jj] : w_hi;
+        }
+        if (__all(ok))
+            wmode = any_two ? W_TWO : W_ONE;
+        else
+            w_hi = 0;
+    };
+    auto w_renew = [&](int tr) __attribute__((always_inline)) {
+        const int ln = lane_again();
+        const int64_t off = (int64_t)tr * C::BK;
+        w_lo = 0;
+        w_hi = ntk;
+#pragma unroll
+        for (int jj = 0; jj < NP; ++jj) {
+            int wel;
+            const int64_t l0 = w_row(ln, jj, wel) * a.k + kb0 + wel;
             const bool in = off + wel < klen;
-            const int64_t l = l0 + (in ? off : 0);
+            const int64_t l = l0 + (in ? off : -wel);
             const int64_t o = residual_offset(a.res, l);
             const bool ok = in && o >= 0;
-            const int64_t cb = (l >> a.res.log2c) << a.res.log2c;
-            const int64_t b0 = (cb - l0 + C::BK - 1) >> 7;
-            const int64_t b1 = (cb + (int64_t(1) << a.res.log2c) - l0 + C::BK - 1) >> 7;
+            const uint32_t at = (uint32_t)l & cmask;  // within the chunk
             const int t_in = (klen - wel + C::BK - 1) >> 7;
-            int t0 = b0 > 0 ? (int)b0 : 0;
-            int t1 = b1 < t_in ? (int)b1 : t_in;
-            wp[jj] = ok ? a.res.pool + (o - (in ? off : 0)) : g_zero16 - off;
-            t0 = ok ? t0 : tr;
-            t1 = ok ? t1 : tr + 1;
-            lo_t = t0 > lo_t ? t0 : lo_t;
-            hi_t = t1 < hi_t ? t1 : hi_t;
-        }
-        if (__all(lo_t <= 0 && hi_t >= ntk)) {
-            wev = -1;
-        } else {
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const int u = __shfl_xor(hi_t, d, 64), v = __shfl_xor(lo_t, d, 64);
-                hi_t = u < hi_t ? u : hi_t;
-                lo_t = v > lo_t ? v : lo_t;
-            }
-            hi_t = __builtin_amdgcn_readfirstlane(hi_t);
-            lo_t = __builtin_amdgcn_readfirstlane(lo_t);
-            wev = hi_t < ntk ? hi_t : (lo_t > 0 ? 0 : -1);  // the walk may wrap to stage 0
+            const int t_out = tr + (int)((cmask - at + C::BK) >> 7);
+            wp[jj] = ok ? a.res.pool + (o - off) : g_zero16 - off;
+            const int t0 = ok ? tr - (int)(at >> 7) : tr;
+            const int t1 = ok ? (t_out < t_in ? t_out : t_in) : tr + 1;
+            w_lo = t0 > w_lo ? t0 : w_lo;
+            w_hi = t1 < w_hi ? t1 : w_hi;
         }
         rare_path_end();
     };
-    static_assert(C::BK == 128, "stage arithmetic of w_pointers");
-    auto issue_w = [&](int tr, int slot) {
+    // W_TWO, at stage tr of a forward walk (a rotated one comes back to stage 0
+    // from the last, where every piece with a second chunk lies in it)
+    auto w_cross = [&](int tr) __attribute__((always_inline)) {
+        w_hi = ntk;
+#pragma unroll
+        for (int jj = 0; jj < NP; ++jj) {
+            const int64_t d = (int64_t)rd[jj] << a.res.log2c;
+            if (tr == 0)
+                wp[jj] -= wb[jj] < ntk ? d : 0;
+            else
+                wp[jj] += wb[jj] == tr ? d : 0;
+            w_hi = wb[jj] > tr && wb[jj] < w_hi ? wb[jj] : w_hi;
+        }
+    };
+    static_assert(C::BK == 128, "stage arithmetic of the residual pointers");
+    auto w_update = [&](int tr) __attribute__((always_inline)) {
+        if (wmode == W_RENEW) {
+            if (__any(tr < w_lo || tr >= w_hi))
+                w_renew(tr);
+        } else {
+            if (wmode == W_TWO && ((tr == 0 && grot > 0) || __any(tr >= w_hi)))
+                w_cross(tr);
+            if (tr >= t_full) {  // the K range ends inside this stage, the walk's last
+                const int ln = lane_again();
+                const int64_t off = (int64_t)tr * C::BK;
+#pragma unroll
+                for (int jj = 0; jj < NP; ++jj) {
+                    int wel;
+                    w_row(ln, jj, wel);
+                    wp[jj] = off + wel < klen ? wp[jj] : g_zero16 - off;
+                }
+            }
+        }
+    };
+    auto issue_w = [&](int tr, int slot) __attribute__((always_inline)) {
         lds_u8 *dst = lds + slot * C::W_SLOT + NP * 1024 * issuer;
         if (tr < t_full) {
 #pragma unroll
@@ -615,8 +689,8 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
             rare_path_end();
         }
         if (MODE == MODE_FULL) {
-            if (tr == wev)
-                w_pointers(tr);
+            if (wmode != W_ONE || tr >= t_full)
+                w_update(tr);
 #pragma unroll
             for (int jj = 0; jj < NP; ++jj)
                 dma16_at<AUX>(wp[jj] + (int64_t)tr * C::BK, dst + C::W_BYTES + jj * 1024);
@@ -725,9 +799,11 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
         }
     };
 
-    if (issues) {
-        // prologue: the steady-state issue of iterations -(WS-1) .. -1, keeping
-        // only stages >= 0, so the counter arithmetic holds from iteration 0
+    // the steady-state issue of iterations -(WS-1) .. -1, keeping only stages
+    // >= 0, so the counter arithmetic holds from iteration 0
+    auto prologue = [&]() __attribute__((always_inline)) {
+        if (MODE == MODE_FULL && a.range)
+            w_first();
 #pragma unroll 1
         for (int u = -(WS - 1); u < 0; ++u) {
             if (u + XS - 1 >= 0 && u + XS - 1 < ntk)
@@ -735,8 +811,9 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
             if (u + WS - 1 < ntk)
                 issue_w(tk(u + WS - 1), u + WS - 1);
         }
-    }
+    };
     if (!SPEC) {
+        prologue();
         for (int t = 0; t < ntk; ++t) {
             wait(t);
             stage_barrier();
@@ -745,6 +822,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     } else if (dma_wave) {
         // separate loops per role keep the DMA state out of the compute waves'
         // registers and the accumulators out of the DMA waves'
+        prologue();
         for (int t = 0; t < ntk; ++t) {
             wait(t);
             stage_barrier();
@@ -950,6 +1028,7 @@ hipError_t launch_gemm_f16(const LinearProblem &p, const LinearPlan &plan, float
     a.partial = partial;
     a.scale = nullptr;
     a.cus = plan.cus;
+    a.range = plan.range_addr;
     a.rotate = p.k % 4096 == 0;
     const bool grouped = p.offsets != nullptr;
     if (plan.variant == GEMM_G5_256x256)
@@ -980,6 +1059,7 @@ hipError_t launch_gemm_fp8(int enc, const uint8_t *xq, const float *scale, const
     a.partial = partial;
     a.scale = scale;
     a.cus = plan.cus;
+    a.range = 0;
     a.rotate = 0;
     if (plan.variant == GEMM_G3_256x256)
         return offsets ? hipErrorInvalidValue : launch_gemm256_fp8(enc, a, stream);

@@ -170,8 +170,13 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
                               (KIND == T_FP8 ? c * 16 : (c & 3) * 16));
     }
     const uint8_t *wp[NW];  // full mode: pointer of the piece of K stage 0
-    int wev = 0;            // full mode: next stage whose pieces need new pointers
-    auto set_tile = [&]() {  // the tile of idx; false when there is none
+    int wev = 0;            // full mode: next stage whose pieces need new pointers (-1: none)
+    // Full mode, K ranges no longer than a chunk: once wknown is set, lane r (and
+    // r + 32) holds how many chunks further than its first one row r of the
+    // wave goes on, less one.
+    bool wknown = false;
+    int32_t wnext = 0;
+    auto set_tile = [&]() __attribute__((always_inline)) {  // the tile of idx; false when there is none
         const uint32_t tl = (blockIdx.x % 8) * per_xcd + idx;
         if (idx >= per_xcd || tl >= total)
             return false;
@@ -199,6 +204,7 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
         xr = make_rsrc(static_cast<const uint8_t *>(a.x) + (xrow0 * a.k + kb0) * C::XB,
                        ((mrow1 - xrow0) * a.k - kb0) * C::XB);
         wev = tk(0);
+        wknown = false;
         if (KIND != T_FULL) {
             // (rows past n lie beyond the resource)
             const int64_t wrow0 = n0 + 32 * wave < a.n ? n0 + 32 * wave : a.n - 1;
@@ -206,39 +212,86 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
         }
         return true;
     };
+    // The stage from which on the residual piece at element `wel` of K stage 0
+    // of row nr lies in the next chunk.
+    auto two_from = [&](const GemmArgs &r, int64_t nr, int wel) __attribute__((always_inline)) {
+        const uint32_t l0 = (uint32_t)nr * (uint32_t)r.k + (uint32_t)kb0 + (uint32_t)wel;
+        const uint32_t c = 1u << r.res.log2c;
+        return (int)((c - (l0 & (c - 1)) + C::BK - 1) >> 6);
+    };
     // Full mode: the pointers of stage tr's pieces, and the next stage in walk
     // order at which any lane's piece leaves its residual chunk or passes the
     // end of the K range (pieces without a source read zeros, stage by stage).
-    auto w_pointers = [&](int tr) {
+    // A lookup waits for the slot table and with it for every load this wave
+    // has in flight, so rows that cross chunks must not cost one per crossing:
+    // both chunks' slots are read once where a row has two at most (MI355X,
+    // 5120 x 6160 in 16 KiB chunks, 1024 tokens: 129 -> 104 us).
+    auto w_pointers = [&](int tr) __attribute__((always_inline)) {
+        const GemmArgs r = rare_args();
         const int ln = lane_again();
         const int64_t off = (int64_t)tr * C::BK;
         int lo_t = 0, hi_t = ntk;  // stages [lo_t, hi_t) keep these pointers
+        if (wknown) {
 #pragma unroll
-        for (int jj = 0; jj < NW; ++jj) {
-            int wel;
-            bool lo;
-            const int64_t nr = w_row(ln, jj, wel, lo);
-            const int64_t l0 = nr * a.k + kb0 + wel;
-            const bool in = off + wel < klen;
-            const uint8_t *p = a.hi + l0;
-            bool ok = in;
-            int t0 = 0, t1 = (klen - wel + C::BK - 1) / C::BK;
-            if (lo) {
-                const int64_t l = l0 + (in ? off : 0);
-                const int64_t o = residual_offset(a.res, l);
-                ok = in && o >= 0;
-                p = a.res.pool + (o - (in ? off : 0));
-                const int64_t cb = (l >> a.res.log2c) << a.res.log2c;
-                const int64_t b0 = (cb - l0 + C::BK - 1) >> 6;
-                const int64_t b1 = (cb + (int64_t(1) << a.res.log2c) - l0 + C::BK - 1) >> 6;
-                t0 = b0 > 0 ? (int)b0 : 0;
-                t1 = b1 < t1 ? (int)b1 : t1;
+            for (int jj = 0; jj < NW; ++jj) {
+                int wel;
+                bool lo;
+                const int64_t nr = w_row(ln, jj, wel, lo);
+                const int t1 = (klen - wel + C::BK - 1) / C::BK;
+                const int b = lo ? two_from(r, nr, wel) : t1;
+                const int64_t d = (int64_t)__shfl(wnext, 8 * jj + (ln >> 3), 64) << r.res.log2c;
+                if (b < t1 && b == (rev ? tr + 1 : tr))
+                    wp[jj] += rev ? -d : d;
+                if (tr >= t1)
+                    wp[jj] = g_zero16 - off;
+                const int t0 = b < t1 && b <= tr ? b : 0;
+                const int tn = b < t1 && b > tr ? b : (t1 > tr ? t1 : ntk);
+                lo_t = t0 > lo_t ? t0 : lo_t;
+                hi_t = tn < hi_t ? tn : hi_t;
             }
-            wp[jj] = ok ? p : g_zero16 - off;
-            t0 = ok ? t0 : tr;
-            t1 = ok ? t1 : tr + 1;
-            lo_t = t0 > lo_t ? t0 : lo_t;
-            hi_t = t1 < hi_t ? t1 : hi_t;
+        } else {
+            bool all_in = true;
+#pragma unroll
+            for (int jj = 0; jj < NW; ++jj) {
+                int wel;
+                bool lo;
+                const int64_t nr = w_row(ln, jj, wel, lo);
+                const int64_t l0 = nr * r.k + kb0 + wel;
+                const bool in = off + wel < klen;
+                const uint8_t *p = r.hi + l0;
+                bool ok = in;
+                int t0 = 0, t1 = (klen - wel + C::BK - 1) / C::BK;
+                if (lo) {
+                    const int64_t l = l0 + (in ? off : -wel);
+                    const int64_t o = residual_offset(r.res, l);
+                    ok = in && o >= 0;
+                    p = r.res.pool + (o - off);
+                    const uint32_t c = 1u << r.res.log2c, at = (uint32_t)l & (c - 1);
+                    const int b1 = tr + (int)((c - at + C::BK - 1) >> 6);
+                    t0 = tr - (int)(at >> 6);
+                    t0 = t0 > 0 ? t0 : 0;
+                    t1 = b1 < t1 ? b1 : t1;
+                }
+                wp[jj] = ok ? p : g_zero16 - off;
+                all_in &= ok;
+                t0 = ok ? t0 : tr;
+                t1 = ok ? t1 : tr + 1;
+                lo_t = t0 > lo_t ? t0 : lo_t;
+                hi_t = t1 < hi_t ? t1 : hi_t;
+            }
+            if (r.range) {
+                const int64_t row = n0 + 32 * wave + (ln & 31);
+                const int64_t f = (row < r.n ? row : r.n - 1) * r.k + kb0;
+                const int64_t ce = ((f >> r.res.log2c) + 1) << r.res.log2c;
+                const bool two = f + klen > ce;
+                if (__any(two)) {
+                    const int64_t o0 = residual_offset(r.res, f);
+                    const int64_t o1 = residual_offset(r.res, two ? ce : f);
+                    wnext = (int32_t)((o1 >> r.res.log2c) - (o0 >> r.res.log2c) - 1);
+                    all_in &= o0 >= 0 && o1 >= 0;
+                }
+                wknown = __all(all_in);
+            }
         }
         if (__all(lo_t <= 0 && hi_t >= ntk)) {
             wev = -1;
@@ -256,7 +309,7 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
         rare_path_end();
     };
     static_assert(KIND != T_FULL || C::BK == 64, "stage arithmetic of w_pointers");
-    auto issue_w = [&](int tr, int slot) {
+    auto issue_w = [&](int tr, int slot) __attribute__((always_inline)) {
         lds_u8 *dst = lds + slot * C::W_SLOT + NW * 1024 * wave;
         if (KIND == T_FULL) {
 #pragma unroll
@@ -286,30 +339,31 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
     f32x4 acc[4][8];
 
     // ---- fragment reads ---------------------------------------------------------
-    const int aoff0 = (wn * (KIND == T_FAST ? 32 : 64) + li) * 128 + ((lg ^ swz8(li)) << 4);
-    const int boff0 = C::X_BASE + (wm * 128 + li) * 128 + ((lg ^ swz8(li)) << 4);
+    // lane part of every fragment address; wave and slot parts are scalar
+    const int foff = li * 128 + ((lg ^ swz8(li)) << 4);
     u32x4 raw[C::RAW];
     u32x4 bv[4][2];
     auto ld = [&](int off) { return *reinterpret_cast<const u32x4 *>(smem + off); };
     auto read_w = [&](int slot) {
-        const int b = slot * C::W_SLOT;
+        const int b = scalar_part(slot * C::W_SLOT + wn * (KIND == T_FAST ? 32 : 64) * 128);
+        const int a0 = b + foff, a1 = b + (foff ^ 64);
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             if (KIND == T_FAST) {
-                raw[nt] = ld(b + ((nt & 1) ? aoff0 ^ 64 : aoff0) + (nt >> 1) * 2048);
+                raw[nt] = ld(((nt & 1) ? a1 : a0) + (nt >> 1) * 2048);
             } else {
-                raw[nt] = ld(b + aoff0 + nt * 2048);
-                raw[(4 + nt) % C::RAW] = ld(b + (aoff0 ^ 64) + nt * 2048);
+                raw[nt] = ld(a0 + nt * 2048);
+                raw[(4 + nt) % C::RAW] = ld(a1 + nt * 2048);
             }
         }
     };
     auto read_b = [&](int slot, int mt) {
-        const int b = slot * C::X_SLOT + mt * 2048;
-        bv[mt & 3][0] = ld(b + boff0);
-        bv[mt & 3][1] = ld(b + (boff0 ^ 64));
+        const int b = scalar_part(C::X_BASE + slot * C::X_SLOT + wm * 128 * 128);
+        bv[mt & 3][0] = ld(b + foff + mt * 2048);
+        bv[mt & 3][1] = ld(b + (foff ^ 64) + mt * 2048);
     };
 
-    auto prologue = [&]() {  // the loads of groups -WS .. -1
+    auto prologue = [&]() __attribute__((always_inline)) {  // the loads of groups -WS .. -1
 #pragma unroll 1
         for (int u = -WS; u < 0; ++u) {
             if (u + XS >= 0 && u + XS < ntk)

@@ -22,6 +22,7 @@ struct GemmArgs {
     float *partial;
     const float *scale;
     int cus;     // compute units of the device (the 256 x 256 tile's grid)
+    int range;   // full mode: a row's residual bytes of one K range span at most two chunks
     int rotate;  // wide-row GEMM: start each block's K walk by weight tile (see gemm4)
 };
 
@@ -167,12 +168,30 @@ __device__ __forceinline__ int unhoisted(int v)
     return v;
 }
 
+// The same for a wave-uniform value, which stays in a scalar register.
+__device__ __forceinline__ int scalar_part(int v)
+{
+    asm("" : "+s"(v));
+    return v;
+}
+
 // lgkmcnt(0).  Scalar loads retire out of order with LDS reads, and a rare
 // path of the stage loop that leaves some pending would make the compiler
 // wait for every LDS read of the common path where it needs only the oldest.
 __device__ __forceinline__ void rare_path_end()
 {
     __builtin_amdgcn_s_waitcnt(0xC07F);
+}
+
+// The kernel's arguments, loaded anew where a rare path needs them: what the
+// stage loop does not use takes no scalar registers there.
+__device__ __forceinline__ GemmArgs rare_args()
+{
+    auto p = (const __attribute__((address_space(4))) void *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    GemmArgs a;
+    __builtin_memcpy(&a, (const void *)p, sizeof(a));
+    return a;
 }
 
 // This lane's index, computed anew where it is called.
