@@ -948,11 +948,7 @@ hipError_t launch_g3_variant(const GemmArgs &a, const LinearPlan &plan, hipStrea
     }
 }
 
-// Grouped calls on the 128-token tile with DMA waves take up to 16 tail rows
-// per expert into its last tile (gemm4_kernel, block_rows): an expert of
-// 129-144 rows reads its weights once, not twice.  Every mode and encoding
-// fits the tail's 16 registers within the 168 that three waves per SIMD allow.
-template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC, int AUX>
+template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC, int TL, int AUX>
 hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped,
                          hipStream_t stream)
 {
@@ -961,7 +957,6 @@ hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped
                                      (unsigned)token_tiles(a.rows, a.experts, true, BM), 1)
                               : dense_grid(nt * plan.splits * ((a.rows + BM - 1) / BM));
     const dim3 block(SPEC ? 768 : 512);
-    constexpr int TL = SPEC && BM == 128 ? 16 : 0;
     if (TL > 0 && grouped)
         hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, SPEC, AUX, TL>), grid, block, 0,
                            stream, a);
@@ -971,18 +966,49 @@ hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped
     return hipGetLastError();
 }
 
+// Whether a call loads its weights nontemporally.  MI355X, time with cached
+// loads over time with nontemporal ones, a rotation of layers of 640 MiB in all
+// / one layer called over and over:
+//   - not where a row is not whole 128-byte lines: a stage's piece then shares
+//     its lines with the next stage's, which fetches them again (28672 x 4112
+//     0.81-0.93 / 0.54-0.76, 16 experts of 3072 x 4112 - / 0.71-0.84);
+//   - not where several token tiles read the weights again a chip's round or more
+//     later: 300 to 1024 tokens - / 0.81-1.00, 8 experts of 36-60 rows on 32-token
+//     tiles 0.94-1.01 / 0.79-0.93.  Grouped calls count as one tile per expert up
+//     to 7/8 of its rows on average (1.01-1.13 below, 0.94-1.01 at 60 of 64), with
+//     tail rows up to all of them (130 of 128 + 16: 1.00-1.06).  The two tiles
+//     of up to 256 dense tokens run side by side: alone 0.90-1.07 / 0.81-0.98, but a pass
+//     over the hidden-4096 set at 256 tokens, 16 sets in turn, gains 1.02 full
+//     and 1.01 fast, as what the smaller layers keep in the cache is not lost;
+//   - from kStreamBytes on.  33-64 tokens 0.96-1.14 / 0.77-1.04.  65-128 tokens
+//     0.99-1.09 / 0.85-0.98 from 80 MiB, 0.90-0.97 / 0.85-0.98 below (4096 x
+//     14336 in fast mode at 128 tokens 28.3 against 26.6 us alone), where what
+//     the smaller layers keep decides again: the pass at 128 tokens in fast
+//     mode 95.8 us, 99.3 with a line at 80 MiB, 16 sets in turn 102.9 and 103.0.
+template <int MODE, int BM, int TL>
+bool streams(const GemmArgs &a, bool grouped)
+{
+    const bool full = MODE == MODE_FULL;
+    const bool lines = a.k % 128 == 0 && (uintptr_t)a.hi % 128 == 0 &&
+                       (!full || ((uintptr_t)a.res.pool % 128 == 0 && a.res.log2c >= 7));
+    const bool once = grouped ? a.rows <= a.experts * (TL > 0 ? BM + TL : BM * 7 / 8)
+                              : a.rows <= 256;
+    return lines && once && a.experts * a.n * a.k * (full ? 2 : 1) >= kStreamBytes;
+}
+
 template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC>
 hipError_t launch_g4(const GemmArgs &a, const LinearPlan &plan, bool grouped, hipStream_t stream)
 {
-    const int64_t planes = MODE == MODE_FULL ? 2 : 1;
-    // Grouped calls whose experts fill more than one token tile on average read
-    // their weights more than once and keep the cached loads (16 experts of
-    // 3072 x 4112, 1400 tokens top-2: 673 us before large layers streamed, 831
-    // with all of them streaming).
-    const bool again = grouped && a.rows > a.experts * (BM + 16);
-    return a.experts * a.n * a.k * planes >= kStreamBytes && !again
-               ? launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, AUX_STREAM>(a, plan, grouped, stream)
-               : launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, AUX_CACHED>(a, plan, grouped, stream);
+    // Grouped calls on the 128-token tile with DMA waves take up to 16 tail rows
+    // per expert into its last tile (gemm4_kernel, block_rows): an expert of
+    // 129-144 rows reads its weights once, not twice.  Every mode and encoding
+    // fits the tail's 16 registers within the 168 that three waves per SIMD allow.
+    constexpr int TL = SPEC && BM == 128 ? 16 : 0;
+    return streams<MODE, BM, TL>(a, grouped)
+               ? launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, TL, AUX_STREAM>(a, plan, grouped,
+                                                                            stream)
+               : launch_g4_aux<MODE, ENC, BM, WS, XS, SPEC, TL, AUX_CACHED>(a, plan, grouped,
+                                                                            stream);
 }
 
 // (token tile, weight slots, token slots) per mode, each within 160 KiB:

@@ -105,8 +105,8 @@ __device__ __attribute__((aligned(16))) const uint8_t g_zero16[16] = {0};
 
 #define DPS_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 
-// Cache policies of a direct-to-LDS load: plain, and nontemporal for the
-// weights of layers beyond kStreamBytes.
+// Cache policies of a direct-to-LDS load: plain, and nontemporal for weights
+// that are read once and do not stay cached (dps_gemm.hip, streams).
 enum { AUX_CACHED = 0, AUX_STREAM = 2 };
 
 __device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)

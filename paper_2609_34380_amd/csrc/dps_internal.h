@@ -70,17 +70,19 @@ enum GemmVariant {
 // 32 weight rows per wave); SKINNY_RING streams it through per-wave LDS rings.
 enum { SKINNY_RING = 2 };
 
-// Kernel choice and work split for one call.  plan_linear is the single
-// place that decides; dps_workspace_bytes and the launch both call it.
-// Weights of at least this many bytes per call (the planes its mode reads) are
-// loaded nontemporally: they cannot stay in the 256 MiB Infinity Cache until
-// the next call anyway, and on MI355X the stream then runs 5-15% faster (28672
-// x 4096 at 8 tokens 24.2 -> 21.9 us fast, 47.6 -> 42.2 full; at 32 tokens
-// 46.3 -> 41.9 full; 4096 x 14336 at 32 tokens 30.5 -> 27.0).  A layer small
-// enough to stay cached between calls loses by it (4096 x 4096 and 6144 x 4096
-// called over and over at 8 tokens: 1.1x the time), so those load plainly.
+// Calls of up to 32 tokens load weights of at least this many bytes (the planes
+// their mode reads) nontemporally.  MI355X, time with cached loads over time
+// with nontemporal ones at 3-32 tokens, a rotation of layers of 640 MiB in all /
+// one layer called over and over, which the 256 MiB Infinity Cache then
+// partly holds: 48-80 MiB 1.00-1.11 / 0.89-1.10, 112-160 MiB 1.04-1.12 /
+// 0.94-1.10, 224 MiB 1.05-1.14 / 0.82-1.03, 448 MiB and more 1.06-1.17 both
+// ways; 24-32 MiB 1.01-1.06 / 0.92-1.02.  A model's layers come round as the
+// rotation does, so the line lies where that one gains and below which a
+// layer alone would lose.
 constexpr int64_t kStreamBytes = int64_t(48) << 20;
 
+// Kernel choice and work split for one call.  plan_linear is the single
+// place that decides; dps_workspace_bytes and the launch both call it.
 struct LinearPlan {
     int kind;
     int variant;       // kernel-family specific tile variant
