@@ -339,28 +339,32 @@ __global__ __launch_bounds__(512) void tile256_kernel(GemmArgs a)
     f32x4 acc[4][8];
 
     // ---- fragment reads ---------------------------------------------------------
-    // lane part of every fragment address; wave and slot parts are scalar
-    const int foff = li * 128 + ((lg ^ swz8(li)) << 4);
+    // Both operands' addresses have one lane part; E4M3 in full mode has a register
+    // for the tokens' only and reaches the weights by a scalar difference.
+    constexpr bool ONE = KIND == T_FULL && ENC == ENC_E4M3;
+    const int abase = wn * (KIND == T_FAST ? 32 : 64) * 128;
+    const int bbase = C::X_BASE + wm * 128 * 128;
+    const int boff0 = bbase + li * 128 + ((lg ^ swz8(li)) << 4);
+    const int aoff0 = ONE ? boff0 : boff0 - bbase + abase;
     u32x4 raw[C::RAW];
     u32x4 bv[4][2];
     auto ld = [&](int off) { return *reinterpret_cast<const u32x4 *>(smem + off); };
     auto read_w = [&](int slot) {
-        const int b = scalar_part(slot * C::W_SLOT + wn * (KIND == T_FAST ? 32 : 64) * 128);
-        const int a0 = b + foff, a1 = b + (foff ^ 64);
+        const int b = ONE ? scalar_part(slot * C::W_SLOT + abase - bbase) : slot * C::W_SLOT;
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             if (KIND == T_FAST) {
-                raw[nt] = ld(((nt & 1) ? a1 : a0) + (nt >> 1) * 2048);
+                raw[nt] = ld(b + ((nt & 1) ? aoff0 ^ 64 : aoff0) + (nt >> 1) * 2048);
             } else {
-                raw[nt] = ld(a0 + nt * 2048);
-                raw[(4 + nt) % C::RAW] = ld(a1 + nt * 2048);
+                raw[nt] = ld(b + aoff0 + nt * 2048);
+                raw[(4 + nt) % C::RAW] = ld(b + (aoff0 ^ 64) + nt * 2048);
             }
         }
     };
     auto read_b = [&](int slot, int mt) {
-        const int b = scalar_part(C::X_BASE + slot * C::X_SLOT + wm * 128 * 128);
-        bv[mt & 3][0] = ld(b + foff + mt * 2048);
-        bv[mt & 3][1] = ld(b + (foff ^ 64) + mt * 2048);
+        const int b = slot * C::X_SLOT + mt * 2048;
+        bv[mt & 3][0] = ld(b + boff0);
+        bv[mt & 3][1] = ld(b + (boff0 ^ 64));
     };
 
     auto prologue = [&]() __attribute__((always_inline)) {  // the loads of groups -WS .. -1
