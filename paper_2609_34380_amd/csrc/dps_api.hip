@@ -143,7 +143,7 @@ dps_status check_weight(const dps_weight *w, int mode)
 namespace dps {
 
 LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_t k,
-                       int64_t experts, int log2c, int cu_count, bool grouped, bool part_filled)
+                       int64_t experts, int log2c, int cu_count, bool grouped, bool ranges256)
 {
     LinearPlan p;
     memset(&p, 0, sizeof(p));
@@ -257,34 +257,49 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         // Dense prefill-sized calls take the 256 x 256 tile when it fills the
         // chip (at least one block per CU), or fills it with two K ranges and
         // K is long enough (>= 8192) for them to pay for their fp32 partials.
-        // MI355X, hidden-4096 set, full mode: gate+up at 1024 / 2048 tokens
-        // 318 / 619 against 345 / 669 us, down at 2048 tokens (two ranges)
-        // 284 against 302, every layer at 8192 tokens 0.82-0.92x the time
-        // (gate+up 1962 against 2340 us).  Slower on it: QKV and O at 2048
-        // tokens (192 and 128 tiles, 4-5%), down at 512 / 1024 tokens (8 / 4
-        // ranges: 89 / 161 against 80 / 154 us) and every decode call up to
-        // 256 tokens (gate+up at 256 tokens 93 against 88 us).
+        // MI355X, full mode, 128 / 256 tile: gate+up at 1024 / 2048 tokens 255 /
+        // 229 and 497 / 450 us, down at 2048 (two ranges) 218 / 212; called
+        // alone it is the slower one just past a round (gate+up at 640 tokens
+        // 168 / 201).
         //
-        // Beyond that it takes calls of more than 256 tokens whose 128 x 128
-        // tiles leave a last round of blocks part full, if one or more K
-        // ranges of at least 2048 elements give its own tiles more than half
-        // of the CUs.  Full mode against the 128 x 128 tile: QKV at 1531 tokens
-        // (144 tiles) 110 against 131 us and at 1024 (96, two ranges) 79
-        // against 87, O and down at 1531 (96, two ranges) 75 / 201 against 83 /
-        // 260, gate+up at 512 / 300 (224) 131 / 125 against 178 / 138.  Not O
-        // at 1024 tokens (64 tiles, four ranges of 1024: 56 against 47) or
-        // QKV at 512 (48: 51 against 43).
+        // Below one round of big tiles, and past one round of 128 x 128 tiles,
+        // the cheaper by this estimate, the big one in up to four K ranges of
+        // at least 2048 elements.  Unit: one K element of a round of 128 x 128
+        // tiles (8 ns).  A round of big tiles takes 3 (four times the work at
+        // half the traffic per flop), each round some elements more to fill and
+        // drain its rings (170 and 200), rows that are not whole 128-byte lines
+        // 1.2 on the 128-row tile, a part-filled round 0.7 + 0.3 x its fill, and
+        // K ranges their fp32 partials, at 8 TB/s (three times that where N does
+        // not allow vector stores).  MI355X under sustained load (65 shapes of
+        // twenty layers, both modes, weights in rotation), 128 / 256 tile in
+        // full mode and the estimate's ratio: 16640 x 4096 at 257 tokens 66 /
+        // 93 us (1.34), O at 2048 78 / 82 (0.99), QKV at 1280 78 / 79 (0.98), at
+        // 2048 117 / 108 (0.90), at 2304 144 / 115 (0.73), down at 1280 1.44x
+        // (0.66).  The line stands at 1 and not lower because within a pass the
+        // 128-row tile also costs its neighbours: it draws more power (O at 2048
+        // tokens in fast mode on it 68 us, on big tiles 74, but gate+up 419
+        // against 393 and the pass 794 against 755).
+        // Decode-sized calls keep the 128-row tile (gate+up at 256 tokens 74 / 82).
         if (!grouped && rows > 256) {
             const int64_t cus = cu_count;
             const int64_t t5 = cdiv(n, 256) * cdiv(rows, 256);
             const int64_t t4 = cdiv(n, 128) * cdiv(rows, 128);
-            int64_t ranges = cus / t5;
-            ranges = ranges < k / 2048 ? ranges : k / 2048;
-            ranges = ranges < 1 ? 1 : (ranges > 4 ? 4 : ranges);
-            if (rows >= 512 && (t5 >= cus || (k >= 8192 && 2 * t5 >= cus)))
+            const auto rounds = [&](int64_t blocks) {
+                return 0.7 * (double)cdiv(blocks, cus) + 0.3 * (double)blocks / (double)cus;
+            };
+            if (rows >= 512 && (t5 >= cus || (k >= 8192 && 2 * t5 >= cus))) {
                 p.variant = GEMM_G5_256x256;
-            else if (part_filled && t5 < cus && t4 > cus && t4 % cus != 0 && 2 * t5 * ranges > cus)
-                p.variant = GEMM_G5_256x256;
+            } else if (ranges256 && t5 < cus && t4 > cus) {
+                const int64_t fit = cus / t5 < k / 2048 ? cus / t5 : k / 2048;
+                const int64_t s5 = fit > 1 ? fit : 1;
+                const double small =
+                    rounds(t4) * ((k % 128 ? 1.2 : 1.0) * (double)k + 170.0);
+                const double partials = (double)s5 * (double)rows * (double)n / 8000.0;
+                const double big = rounds(t5 * s5) * (3.0 * (double)k / (double)s5 + 200.0) +
+                                   (s5 == 1 ? 0.0 : (n % 4 ? 3.0 : 1.0) * partials);
+                if (s5 <= 4 && big < small)
+                    p.variant = GEMM_G5_256x256;
+            }
         }
         const bool g5 = p.variant == GEMM_G5_256x256;
         const int64_t tiles =
@@ -494,7 +509,7 @@ dps_status run_linear(int mode, uint32_t flags, const uint16_t *x, const int32_t
     size_t need = plan.ws_partial + plan.ws_quant;
     if (need > 0 && (ws == nullptr || ws_bytes < need)) {
         // A workspace sized for longer calls, whose plans split no K, can be
-        // too small for a part-filled grid's K ranges: the 128-row tile serves.
+        // too small for this one's K ranges: the 128-row tile serves.
         plan = dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts, log2c,
                                 current_cu_count(), grouped, false);
         need = plan.ws_partial + plan.ws_quant;

@@ -94,11 +94,11 @@ struct LinearPlan {
     size_t ws_quant;   // E4M3 activations + row scales, bytes
 };
 
-// part_filled: calls whose 128-row tiles part-fill a round may take the 256 x
-// 256 tile in K ranges (which needs a workspace for their partials).
+// ranges256: the 256 x 256 tile may be split into K ranges (which needs a
+// workspace for their partials).
 LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_t k,
                        int64_t experts, int log2c, int cu_count, bool grouped,
-                       bool part_filled = true);
+                       bool ranges256 = true);
 
 hipError_t launch_skinny(const LinearProblem &p, const LinearPlan &plan, float *partial,
                          hipStream_t stream);

@@ -204,7 +204,7 @@ def test_plan_info_names_the_kernel_of_each_shape_class(lib):
     assert p["kernel"] == "decode"
     p = d.plan_info(0, "fp16", 256, 28672, 4096)
     assert (p["kernel"], p["tile_rows"], p["tile_tokens"], p["splits"]) == ("gemm_f16", 128, 128, 1)
-    p = d.plan_info(0, "fp16", 2048, 6144, 4096)       # 192 large tiles: the 128 x 128 tile
+    p = d.plan_info(0, "fp16", 1024, 4096, 4096)       # one round of the 128 x 128 tile
     assert (p["kernel"], p["tile_rows"], p["tile_tokens"], p["splits"]) == ("gemm_f16", 128, 128, 1)
     p = d.plan_info(0, "fp16", 2048, 28672, 4096)      # 896 large tiles fill the chip
     assert (p["kernel"], p["tile_rows"], p["tile_tokens"], p["splits"]) == ("gemm_f16", 256, 256, 1)
@@ -226,6 +226,34 @@ def test_plan_info_names_the_kernel_of_each_shape_class(lib):
         p = d.plan_info(mode, act, m, n, k)
         ws = d.workspace_bytes(mode, d._act_flag(act), m, n, k)
         assert (p["splits"] > 1) == (ws >= p["splits"] * m * n * 4 > 0), (m, n, k, p, ws)
+
+
+@pytest.mark.parametrize("m,n,k,tile,splits", [
+    (300, 16640, 4096, 128, 1),    # 130 big tiles for what 1.5 rounds of small ones do
+    (384, 20000, 4096, 128, 1),
+    (700, 8190, 4112, 128, 1),     # partials without vector stores do not pay
+    (700, 8192, 4112, 256, 2),
+    (1000, 6144, 512, 128, 1),     # short K
+    (1531, 6144, 4096, 256, 1),
+    (1920, 6144, 4096, 256, 1),    # the same big tiles at ...
+    (2048, 6144, 4096, 256, 1),    # ... three whole rounds of small ones
+    (1531, 4096, 4096, 256, 2),
+    (2048, 4096, 4096, 256, 2),
+    (512, 28672, 4096, 256, 1),
+    (500, 28672, 8192, 256, 1),    # below 512 tokens too
+    (1280, 4096, 14336, 256, 3),
+    (768, 4096, 14336, 128, 1),    # within one round of small tiles
+])
+def test_prefill_tile_by_estimate(lib, m, n, k, tile, splits):
+    """Both modes share the choice; the workspace query follows it, and no call
+    asks for more scratch than the static array holds."""
+    from paper_2609_34380_amd import dps as d
+    for mode in (d.MODE_FULL, d.MODE_FAST):
+        p = d.plan_info(mode, "fp16", m, n, k)
+        assert (p["tile_rows"], p["tile_tokens"], p["splits"]) == (tile, tile, splits)
+        need = d.workspace_bytes(mode, d.ACT_FP16, m, n, k)
+        assert need == (0 if splits == 1 else -(-splits * m * n * 4 // 256) * 256)
+        assert need <= 64 << 20
 
 
 def test_plan_info_rejects_bad_arguments(lib):

@@ -56,8 +56,8 @@ def test_slots_outside_the_pool_read_as_zero(log2c):
 
 
 @pytest.mark.parametrize("m,n,k,splits", [
-    (300, 16650, 464, 1),     # 132 tiles just past one token tile, ragged every way
-    (700, 8190, 4112, 2),     # 96 tiles in two K ranges, N not a multiple of 4
+    (700, 16650, 464, 1),     # 198 tiles, ragged every way
+    (700, 8190, 8208, 2),     # 96 tiles in two K ranges, N not a multiple of 4
 ])
 @pytest.mark.parametrize("mode", [dps.MODE_FAST, dps.MODE_FULL], ids=["fast", "full"])
 def test_part_filled_grids_take_the_tile(m, n, k, splits, mode):
@@ -75,7 +75,7 @@ def test_part_filled_grids_take_the_tile(m, n, k, splits, mode):
 def test_small_workspace_still_runs():
     """A call whose K ranges need a workspace runs with a smaller one, on the
     128-row tile; a call that cannot do without stays refused."""
-    m, n, k = 700, 8190, 4112
+    m, n, k = 700, 8190, 8208
     ws = torch.empty(256, dtype=torch.uint8, device=DEV)
     assert dps.workspace_bytes(dps.MODE_FAST, dps.ACT_FP16, m, n, k, 1) > ws.numel()
     nst = Nested(workloads.weight_fp16(n, k, seed=83), 14, slot_seed=3)
