@@ -220,7 +220,8 @@ size_t dps_workspace_bytes(int mode, uint32_t flags, int64_t rows, int64_t n,
  *   ws     device scratch of ws_bytes >= dps_workspace_bytes(...), 256-byte
  *          aligned; may be NULL when that is 0.  A call of more than 256
  *          tokens that dps_workspace_bytes gives scratch for K ranges of the
- *          256 x 256 tile also runs with less, on the 128-row tile. */
+ *          256 x 256 tile also runs with less (or off the alignment), on the
+ *          128-row tile. */
 dps_status dps_linear(int mode, uint32_t flags, const uint16_t *x, int64_t m,
                       const dps_weight *w, uint16_t *y, void *ws, size_t ws_bytes,
                       void *stream);

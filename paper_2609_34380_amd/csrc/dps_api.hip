@@ -507,9 +507,10 @@ dps_status run_linear(int mode, uint32_t flags, const uint16_t *x, const int32_t
     dps::LinearPlan plan = dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts, log2c,
                                             current_cu_count(), grouped);
     size_t need = plan.ws_partial + plan.ws_quant;
-    if (need > 0 && (ws == nullptr || ws_bytes < need)) {
+    if (need > 0 && (ws == nullptr || ws_bytes < need || !aligned(ws, 256))) {
         // A workspace sized for longer calls, whose plans split no K, can be
-        // too small for this one's K ranges: the 128-row tile serves.
+        // too small for this one's K ranges, and one that no call needed may
+        // not be aligned: the 128-row tile serves.
         plan = dps::plan_linear(mode, flags, rows, w->n, w->k, w->experts, log2c,
                                 current_cu_count(), grouped, false);
         need = plan.ws_partial + plan.ws_quant;

@@ -87,3 +87,20 @@ def test_small_workspace_still_runs():
     assert dps.workspace_bytes(dps.MODE_FAST, dps.ACT_FP16, 40, n, k, 1) > ws.numel()
     with pytest.raises(dps.DpsError):
         dps.linear(x[:40].contiguous().to(DEV), nst.nw, dps.MODE_FAST, workspace=ws)
+
+
+def test_misaligned_workspace_still_runs():
+    """So does one off its alignment, in a call that the 128-row tile serves
+    without any; where that tile needs one too, it is refused."""
+    m, n, k = 1300, 4096, 4096
+    assert dps.plan_info(dps.MODE_FAST, "fp16", m, n, k)["splits"] == 2
+    need = dps.workspace_bytes(dps.MODE_FAST, dps.ACT_FP16, m, n, k, 1)
+    ws = torch.empty(need + 16, dtype=torch.uint8, device=DEV)[16:]
+    nst = Nested(workloads.weight_fp16(n, k, seed=85), 14, slot_seed=3)
+    x = workloads.activations_fp16(m, k, seed=86)
+    y = dps.linear(x.to(DEV), nst.nw, dps.MODE_FAST, workspace=ws)
+    rows = np.concatenate([np.arange(0, m, 67), [m - 1]])
+    ref = oracle.linear_rows(oracle.FAST, u16(x), rows, nst.hi_ref, None)
+    assert_close(y[torch.from_numpy(rows).to(DEV)], ref)
+    with pytest.raises(dps.DpsError):
+        dps.linear(x[:40].contiguous().to(DEV), nst.nw, dps.MODE_FAST, workspace=ws)
