@@ -224,19 +224,21 @@ hipError_t launch_mr(const GemvArgs &a, const LinearPlan &plan, hipStream_t stre
 // the weight rows it serves (MI355X, four tokens on the hidden-4096 QKV and
 // O layers: 8-wave blocks 0.75-0.99x the time of 4-wave ones).  One row
 // per wave up to 8192 rows (more waves in flight), two beyond -- except one
-// token in full mode, whose two planes give a wave enough loads in flight
-// with one row (28672 x 4096: 38.8 us against 40.9, E4M3 40.6 against 44.4,
-// 57344 x 8192: 139 against 143; fast mode 25.0 against 21.4, two tokens
-// even).
+// token in full mode, whose two planes give a wave enough loads in flight with
+// one row if it is long: from 1536 elements 0.97-1.17x the speed of two rows
+// (28672 x 4096 38.8 us against 40.9, E4M3 40.6 against 44.4; fourteen layers,
+// geometric mean 1.05), at 256-1024 0.91-1.08 (10240 x 512 0.92), where what a
+// wave has to set up for a row counts; fast mode 25.0 against 21.4 us, two
+// tokens even.
+constexpr int64_t kOneRowK = 1536;
+
 template <int MODE, int ENC, int M>
 hipError_t launch_m(const GemvArgs &a, const LinearPlan &plan, hipStream_t stream)
 {
     constexpr int W = M <= 2 ? 4 : 8;
-    if constexpr (MODE == MODE_FULL && M == 1)
-        return launch_mr<MODE, ENC, M, 1, W>(a, plan, stream);
-    else
-        return a.n <= 8192 ? launch_mr<MODE, ENC, M, 1, W>(a, plan, stream)
-                           : launch_mr<MODE, ENC, M, 2, W>(a, plan, stream);
+    const bool one = a.n <= 8192 || (MODE == MODE_FULL && M == 1 && a.k >= kOneRowK);
+    return one ? launch_mr<MODE, ENC, M, 1, W>(a, plan, stream)
+               : launch_mr<MODE, ENC, M, 2, W>(a, plan, stream);
 }
 
 template <int MODE, int ENC>

@@ -2,7 +2,7 @@
 
 The 16-row kernel stages eight token rows up to eight tokens and sixteen
 beyond; the row GEMV takes one weight row per wave for one token in full mode
-at every layer size.  Both against the oracle on ragged K and row counts.  The
+beyond 8192 rows of 1536 elements on, two below.  Both against the oracle on ragged K and row counts.  The
 encoding choice reads four vectors per thread: a misfit in any vector of a
 layer that ends inside a block's share flips it."""
 import pytest
@@ -35,6 +35,8 @@ def test_token_rows_staged(n, k, log2c, enc, m, mode):
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("n,k,log2c,enc", [
     (8193, 1040, 10, dps.ENC_E5M2),   # just past the two-row rule, a part-filled last block
+    (8203, 1536, 14, dps.ENC_E5M2),   # the shortest rows taken one by one, and just below
+    (8203, 1520, 14, dps.ENC_E4M3),
     (8203, 2064, 14, dps.ENC_E4M3),
 ])
 def test_one_token_large_layers(n, k, log2c, enc, mode):
