@@ -35,8 +35,8 @@ __device__ __forceinline__ bool e4m3_fits(uint32_t word16)
     return (word16 & 0x7FFFu) < 0x3F80u;
 }
 
-// A result nothing reads soon (planes of a loaded layer, merged weights):
-// stored past the caches, which the layer being read then keeps.
+// A result nothing reads soon (the planes of a loaded layer): stored past the
+// caches, which the layer being read then keeps.
 __device__ __forceinline__ void store_stream(void *p, u32x4 v)
 {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));

@@ -25,59 +25,52 @@ namespace dps {
 namespace {
 
 // ------------------------------------------------------------------------------
-// Eight-wave LDS-DMA GEMM (two waves per SIMD), fast mode with FP8 activations
+// 256 x 128 LDS-DMA GEMM, fast mode with FP8 activations
 // ------------------------------------------------------------------------------
-// Block tile BN weight rows x BM tokens, waves in a WN x WM grid, each wave
-// (BN/WN) x (BM/WM).  A stage covers 128 K elements (one 16x16x128 MFMA
-// step).  Stages stream global -> LDS by direct-to-LDS loads, weights and
-// tokens through separate rings of WS and XS slots (the 256 x 256 tile keeps
-// two weight stages in flight within 160 KiB), one barrier per stage.  LDS
-// rows hold 16-byte chunks at
-// slot chunk ^ swz(row), swz(row) = (row / 2) % 8 for the 128-byte rows, so
-// the 16 rows a fragment read touches land in 16 distinct 16-byte bank
-// groups.  Lane (i, g): A = weight row i and B = token row i, bytes
-// 16g .. 16g+15 and 64+16g .. 64+16g+15 of the stage (the MFMA's 32-byte K
-// slice of lane group g, permuted alike in both operands).  Reading chunks
-// 2g and 2g+1 instead cost ~4 LDS bank-conflict cycles per read (rocprofv3
+// Block tile 256 weight rows x 128 tokens, eight compute waves (two per SIMD)
+// in a 4 x 2 grid of 64 x 64 each.  A stage covers 128 K elements (one
+// 16x16x128 MFMA step).  Stages stream global -> LDS by direct-to-LDS loads
+// into rings of three slots (144 KiB), one barrier per stage; four more waves
+// (one per SIMD) only issue those loads and wait for them: a wave that issues
+// vector-memory instructions stalls on them, and the compute waves then keep
+// the matrix cores busy instead.  LDS rows hold 16-byte chunks at slot
+// chunk ^ swz8(row), so the 16 rows a fragment read touches land in 16
+// distinct 16-byte bank groups.  Lane (i, g): A = weight row i and B = token
+// row i, bytes 16g .. 16g+15 and 64+16g .. 64+16g+15 of the stage (the MFMA's
+// 32-byte K slice of lane group g, permuted alike in both operands).  Reading
+// chunks 2g and 2g+1 instead cost ~4 LDS bank-conflict cycles per read (rocprofv3
 // SQ_LDS_BANK_CONFLICT) and 3-5% of the prefill time on MI355X.
-template <int BN_, int BM_, int WN, int WM, int WS, int XS, bool DW>
 struct G3 {
-    static constexpr int BK = 128;
-    static constexpr int ROW = BK;                   // bytes per row, both operands
-    static constexpr int W_BYTES = BN_ * ROW;
-    static constexpr int X_BYTES = BM_ * ROW;
-    static constexpr int X_BASE = W_BYTES * WS;      // weight ring, then token ring
-    static constexpr int LDS = X_BASE + X_BYTES * XS;
-    static constexpr int NWAVES = WN * WM;                  // compute waves
-    static constexpr int NISS = DW ? 4 : NWAVES;            // waves that issue the DMA
-    static constexpr int W_INSTR = W_BYTES / 1024 / NISS;
-    static constexpr int X_INSTR = X_BYTES / 1024 / NISS;
-    // Iteration t issues tokens of stage t+XS-1, then weights of stage
-    // t+WS-1 (XS <= WS).  At the wait for stage t the instructions issued
-    // after the later of tokens t and weights t may stay outstanding.
-    static constexpr int OUTSTANDING =
-        (XS < WS ? W_INSTR : 0) + (XS - 2) * (W_INSTR + X_INSTR);
-    static_assert(WS >= 2 && XS >= 2 && XS <= WS, "ring depths");
-    static constexpr int TN = BN_ / WN, TM = BM_ / WM;
-    static constexpr int NT = TN / 16, MT = TM / 16;
-    static_assert(W_BYTES % (1024 * NISS) == 0 && X_BYTES % (1024 * NISS) == 0, "tiling");
+    static constexpr int BN = 256, BM = 128;          // block tile
+    static constexpr int WN = 4, WM = 2;              // compute waves
+    static constexpr int S = 3;                       // ring slots
+    static constexpr int BK = 128;                    // bytes (K elements) per row and stage
+    static constexpr int W_BYTES = BN * BK;
+    static constexpr int X_BYTES = BM * BK;
+    static constexpr int X_BASE = W_BYTES * S;        // weight ring, then token ring
+    static constexpr int LDS = X_BASE + X_BYTES * S;
+    static constexpr int NISS = 4;                    // waves that issue the DMA
+    static constexpr int NW = W_BYTES / 1024 / NISS;  // their instructions per stage
+    static constexpr int NX = X_BYTES / 1024 / NISS;
+    // Iteration t issues tokens, then weights of stage t + S - 1; at the wait
+    // for stage t the groups of the later stages may stay outstanding.
+    static constexpr int OUTSTANDING = (S - 2) * (NW + NX);
+    static constexpr int NT = BN / WN / 16, MT = BM / WM / 16;
+    static constexpr int THREADS = (WN * WM + NISS) * 64;
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 
-__device__ __forceinline__ int g3_swz(int r) { return (r >> 1) & 7; }
-
-// TAIL (grouped calls on the 256 x 128 tile): as in the FP16 wide-row GEMM,
-// an expert's last token tile may run up to TAIL rows past 128 (block_rows);
-// each compute wave loads the 32-byte K slices of the 16 tail tokens for
+// TAIL (grouped calls): as in the FP16 wide-row GEMM, an expert's last token
+// tile may run up to TAIL rows past 128 (block_rows); each compute wave loads the 32-byte K slices of the 16 tail tokens for
 // every stage straight from memory into registers and runs them against
 // two of its four weight fragments (token half 0 the first two, half 1 the
 // last two): 18 MFMAs per stage instead of 16.
-template <int ENC, int BN_, int BM_, int WN, int WM, int WS, int XS, bool DW, int TAIL = 0>
-__global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(GemmArgs a)
+template <int ENC, int TAIL>
+__global__ __launch_bounds__(G3::THREADS) void gemm3_kernel(GemmArgs a)
 {
-    using C = G3<BN_, BM_, WN, WM, WS, XS, DW>;
-    static_assert(TAIL == 0 || (TAIL == 16 && DW && BM_ == 128 && WM == 2 && C::NT == 4),
-                  "tail rows: the 256 x 128 tile with DMA waves");
+    using C = G3;
+    constexpr int WN = C::WN, WM = C::WM, S = C::S;
+    static_assert(TAIL == 0 || TAIL == 16, "one 16-token fragment");
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::LDS];
     lds_u8 *const lds = (lds_u8 *)smem;
 
@@ -86,22 +79,18 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15;
     const int lg = lane >> 4;
-    // DW: four more waves (one per SIMD) only issue the direct-to-LDS loads
-    // and wait for them; a wave that issues vector-memory instructions stalls
-    // on them, and the compute waves then keep the matrix cores busy instead
-    const bool dma_wave = DW && wave >= C::NWAVES;
-    const int iss = DW ? wave - C::NWAVES : wave;  // index among the issuing waves
-    const bool issues = !DW || dma_wave;
+    const bool dma_wave = wave >= WN * WM;
+    const int iss = wave - WN * WM;  // index among the issuing waves
 
     int64_t e, mrow0, mrow1;
-    int64_t mtail1 = 0;  // end of the tail rows (TAIL blocks whose range passes BM_)
+    int64_t mtail1 = 0;  // end of the tail rows (TAIL blocks whose range passes BM)
     int ntile, s;
     if (a.offsets) {
         // grouped: grid.y walks the experts' token tiles, grid.x the weight
         // tiles times the K ranges
-        if (!block_rows(a, e, mrow0, mtail1, BM_, TAIL))
+        if (!block_rows(a, e, mrow0, mtail1, C::BM, TAIL))
             return;
-        mrow1 = mrow0 + BM_ < mtail1 ? mrow0 + BM_ : mtail1;
+        mrow1 = mrow0 + C::BM < mtail1 ? mrow0 + C::BM : mtail1;
         ntile = blockIdx.x / a.splits;
         s = blockIdx.x % a.splits;
     } else {
@@ -109,8 +98,8 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         // x is given the contiguous tile range [x * per_xcd, (x+1) * per_xcd),
         // walked with the token tile fastest.  Blocks sharing a weight tile
         // then run together on one XCD and fetch it into that XCD's L2 once.
-        const uint32_t mtiles = (uint32_t)((a.rows + BM_ - 1) / BM_);
-        const uint32_t ntiles = (uint32_t)((a.n + BN_ - 1) / BN_);
+        const uint32_t mtiles = (uint32_t)((a.rows + C::BM - 1) / C::BM);
+        const uint32_t ntiles = (uint32_t)((a.n + C::BN - 1) / C::BN);
         const uint32_t total = mtiles * ntiles * (uint32_t)a.splits;
         const uint32_t per_xcd = (total + 7) / 8;
         const uint32_t t0 = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
@@ -119,11 +108,11 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         ntile = (int)((t0 / mtiles) % ntiles);
         s = (int)(t0 / (mtiles * ntiles));
         e = 0;
-        mrow0 = (int64_t)(t0 % mtiles) * BM_;
-        mrow1 = mrow0 + BM_ < a.rows ? mrow0 + BM_ : a.rows;
+        mrow0 = (int64_t)(t0 % mtiles) * C::BM;
+        mrow1 = mrow0 + C::BM < a.rows ? mrow0 + C::BM : a.rows;
         mtail1 = mrow1;
     }
-    const int64_t n0 = (int64_t)ntile * BN_;
+    const int64_t n0 = (int64_t)ntile * C::BN;
     const int64_t kb0 = (int64_t)s * a.ksplit;
     const int64_t ke = kb0 + a.ksplit < a.k ? kb0 + a.ksplit : a.k;
     const int klen = (int)(ke - kb0);
@@ -132,15 +121,15 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     const int t_full = a.k <= kMaxOffsetK ? klen / C::BK : 0;
 
     // Tail rows: lane (i, g) of a compute wave reads bytes 16g .. 16g+15 and
-    // 64+16g .. 64+16g+15 of each stage of token mrow0 + BM_ + i (the slice
+    // 64+16g .. 64+16g+15 of each stage of token mrow0 + 128 + i (the slice
     // its MFMA operand takes).  K being a multiple of 16, a piece is inside
     // [kb0, ke) whenever it starts there; otherwise the lane reads the row's
     // first 16 bytes of the range and zeroes them.  Lanes past the tail read
     // its last row, whose sums they do not store.
-    const bool has_tail = TAIL > 0 && mtail1 > mrow0 + BM_;
+    const bool has_tail = TAIL > 0 && mtail1 > mrow0 + C::BM;
     const uint8_t *xt = static_cast<const uint8_t *>(a.x);
     if (has_tail) {
-        int64_t m = mrow0 + BM_ + li;
+        int64_t m = mrow0 + C::BM + li;
         m = m < mtail1 ? m : mtail1 - 1;
         xt += m * a.k + kb0;
     }
@@ -150,8 +139,8 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     // tile (j = its instructions per stage times iss, plus jj): lane -> row
     // 8j + lane/8, slot lane%8.  Rows past the operand's end lie beyond its
     // resource; what they leave in LDS is never stored.
-    constexpr int NW = C::W_INSTR, NX = C::X_INSTR;
-    const int wr0 = issues ? 8 * NW * iss : 0, xr0 = issues ? 8 * NX * iss : 0;
+    constexpr int NW = C::NW, NX = C::NX;
+    const int wr0 = dma_wave ? 8 * NW * iss : 0, xr0 = dma_wave ? 8 * NX * iss : 0;
     const int64_t wrow0 = n0 + wr0 < a.n ? n0 + wr0 : a.n - 1;
     const int64_t xrow0 = mrow0 + xr0 < mrow1 ? mrow0 + xr0 : mrow1 - 1;
     const rsrc_t wr = make_rsrc(a.hi + (e * a.n + wrow0) * a.k + kb0, (a.n - wrow0) * a.k - kb0);
@@ -162,7 +151,7 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
 #pragma unroll
     for (int par = 0; par < 2; ++par)
         off[par] = (uint32_t)((lane >> 3) * a.k +
-                              ((lane & 7) ^ g3_swz(8 * par + (lane >> 3))) * 16);
+                              ((lane & 7) ^ swz8(8 * par + (lane >> 3))) * 16);
     static_assert(NW % 2 == 0 && NX % 2 == 0, "instruction parity");
     auto issue_op = [&](auto n_c, const rsrc_t &r, const uint8_t *base, int64_t row0, int64_t row1,
                         int tr, lds_u8 *dst) {
@@ -176,7 +165,7 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
 #pragma unroll
             for (int jj = 0; jj < N; ++jj) {
                 const int rr = 8 * jj + (ln >> 3);
-                const int kk = tr * C::BK + ((ln & 7) ^ g3_swz(rr)) * 16;
+                const int kk = tr * C::BK + ((ln & 7) ^ swz8(rr)) * 16;
                 const bool ok = row0 + rr < row1 && kk < klen;
                 const uint8_t *src = base + (row0 + rr) * a.k + kb0 + kk;
                 dma16_at<AUX_CACHED>(ok ? (const void *)src : (const void *)g_zero16,
@@ -195,17 +184,15 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
             issue_op(std::integral_constant<int, NX>{}, xr, static_cast<const uint8_t *>(a.x),
                      mrow0 + xr0, mrow1, t, lds + C::X_BASE + slot * C::X_BYTES + NX * 1024 * iss);
     };
-    // Iteration t issues tokens of stage t + XS - 1, then weights of stage t +
-    // WS - 1, into the slots that stage t - 1 has left.
-    int iws = WS - 1, ixs = XS - 1;  // their slots
+    // Iteration t fills the slots that stage t - 1 has left.
+    int is = S - 1;  // the slot of stage t + S - 1
     auto issue = [&](int t) {
-        issue_x(t + XS - 1, ixs);
-        issue_w(t + WS - 1, iws);
-        iws = iws + 1 < WS ? iws + 1 : 0;
-        ixs = ixs + 1 < XS ? ixs + 1 : 0;
+        issue_x(t + S - 1, is);
+        issue_w(t + S - 1, is);
+        is = is + 1 < S ? is + 1 : 0;
     };
     auto wait = [&](int t) {  // tokens t and weights t have landed
-        if (t + WS - 1 <= ntk)
+        if (t + S - 1 <= ntk)
             DPS_WAIT_VMCNT(C::OUTSTANDING);
         else
             DPS_WAIT_VMCNT(0);
@@ -220,17 +207,14 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         for (int j = 0; j < C::MT; ++j)
             acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // prologue: the steady-state issue of iterations -(WS-1) .. -1, keeping
-    // only stages >= 0
-#pragma unroll 1
-    for (int u = -(WS - 1); u < 0 && issues; ++u) {
-        if (u + XS - 1 >= 0)
-            issue_x(u + XS - 1, u + XS - 1);
-        issue_w(u + WS - 1, u + WS - 1);
-    }
-    if (DW && dma_wave) {
+    if (dma_wave) {
         // the DMA waves' own loop keeps their state out of the compute waves'
         // registers (and the accumulators out of theirs)
+#pragma unroll 1
+        for (int u = 0; u < S - 1; ++u) {
+            issue_x(u, u);
+            issue_w(u, u);
+        }
         for (int t = 0; t < ntk; ++t) {
             wait(t);
             stage_barrier();
@@ -241,16 +225,13 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     }
     f32x4 tacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
     const int wmu = __builtin_amdgcn_readfirstlane(wm);  // token half, wave-uniform
-    // one stage of a compute wave, which without DW also issues its share of
-    // the DMA (tail_c: std::true_type in blocks with tail rows)
-    int cws = 0, cxs = 0;  // slots of the stage being multiplied
+    // one stage of a compute wave (tail_c: std::true_type in blocks with tail rows)
+    // slots of the stage being multiplied (equal, but kept apart: with one counter
+    // the compiler reads fragments in another order, 1-2% slower)
+    int cws = 0, cxs = 0;
     auto stage = [&](int t, auto tail_c) {
         constexpr bool TL = decltype(tail_c)::value;
-        if (!DW)
-            wait(t);
         stage_barrier();
-        if (!DW)
-            issue(t);
         u32x4 tp = {0u, 0u, 0u, 0u}, tq = {0u, 0u, 0u, 0u};
         if constexpr (TL) {
             const int toff = t * C::BK + 16 * lg;
@@ -262,14 +243,14 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         }
         const uint8_t *st = smem + cws * C::W_BYTES;
         const uint8_t *xs = smem + C::X_BASE + cxs * C::X_BYTES;
-        cws = cws + 1 < WS ? cws + 1 : 0;
-        cxs = cxs + 1 < XS ? cxs + 1 : 0;
+        cws = cws + 1 < S ? cws + 1 : 0;
+        cxs = cxs + 1 < S ? cxs + 1 : 0;
         i32x8 av[C::NT];
 #pragma unroll
         for (int nt = 0; nt < C::NT; ++nt) {
-            const int r = wn * C::TN + nt * 16 + li;
-            const uint8_t *row = st + r * C::ROW;
-            const int sw = g3_swz(r);
+            const int r = wn * 64 + nt * 16 + li;
+            const uint8_t *row = st + r * C::BK;
+            const int sw = swz8(r);
             const u32x4 p = *reinterpret_cast<const u32x4 *>(row + ((lg ^ sw) << 4));
             const u32x4 q = *reinterpret_cast<const u32x4 *>(row + (((4 + lg) ^ sw) << 4));
             av[nt] = i32x8{(int)p.x, (int)p.y, (int)p.z, (int)p.w,
@@ -277,9 +258,9 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
         }
 #pragma unroll
         for (int mt = 0; mt < C::MT; ++mt) {
-            const int r = wm * C::TM + mt * 16 + li;
-            const uint8_t *row = xs + r * C::ROW;
-            const int sw = g3_swz(r);
+            const int r = wm * 64 + mt * 16 + li;
+            const uint8_t *row = xs + r * C::BK;
+            const int sw = swz8(r);
             const u32x4 p = *reinterpret_cast<const u32x4 *>(row + ((lg ^ sw) << 4));
             const u32x4 q = *reinterpret_cast<const u32x4 *>(row + (((4 + lg) ^ sw) << 4));
             const i32x8 bv = {(int)p.x, (int)p.y, (int)p.z, (int)p.w,
@@ -313,19 +294,19 @@ __global__ __launch_bounds__(WN * WM * 64 + (DW ? 256 : 0)) void gemm3_kernel(Ge
     constexpr float wscale = ENC == ENC_E4M3 ? 0.00390625f : 1.f;
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
-        const int64_t m = mrow0 + wm * C::TM + mt * 16 + li;
+        const int64_t m = mrow0 + wm * 64 + mt * 16 + li;
         const float sc = m < mrow1 ? a.scale[m] * wscale : 0.f;
 #pragma unroll
         for (int nt = 0; nt < C::NT; ++nt)
-            store_tile_out(a, s, m, n0 + wn * C::TN + nt * 16 + lg * 4, acc[nt][mt] * sc,
+            store_tile_out(a, s, m, n0 + wn * 64 + nt * 16 + lg * 4, acc[nt][mt] * sc,
                            mrow1);
     }
     if (TAIL > 0 && has_tail) {
-        const int64_t m = mrow0 + BM_ + li;
+        const int64_t m = mrow0 + C::BM + li;
         const float sc = m < mtail1 ? a.scale[m] * wscale : 0.f;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            store_tile_out(a, s, m, n0 + wn * C::TN + (2 * wmu + j) * 16 + lg * 4,
+            store_tile_out(a, s, m, n0 + wn * 64 + (2 * wmu + j) * 16 + lg * 4,
                            tacc[j] * sc, mtail1);
     }
 }
@@ -894,7 +875,7 @@ __global__ __launch_bounds__(SPEC ? 768 : 512) void gemm4_kernel(GemmArgs a)
     }
 }
 
-int64_t token_tiles(int64_t rows, int64_t experts, bool grouped, int bm = BM)
+int64_t token_tiles(int64_t rows, int64_t experts, bool grouped, int bm)
 {
     return grouped ? (rows + bm - 1) / bm + experts : (rows + bm - 1) / bm;
 }
@@ -921,31 +902,22 @@ int gemm_tokens_per_block(int variant)
 
 namespace {
 
-template <int ENC, int BN_, int BM_, int WN, int WM, int WS, int XS, bool DW>
+template <int ENC>
 hipError_t launch_g3(const GemmArgs &a, const LinearPlan &plan, hipStream_t stream)
 {
-    const int64_t nt = (a.n + BN_ - 1) / BN_;
-    const dim3 grid = a.offsets ? dim3((unsigned)(nt * plan.splits),
-                                       (unsigned)token_tiles(a.rows, a.experts, true, BM_), 1)
-                                : dense_grid(nt * plan.splits * ((a.rows + BM_ - 1) / BM_));
-    // grouped calls on the 256 x 128 tile take up to 16 tail rows per expert
-    constexpr int TL = DW && BM_ == 128 ? 16 : 0;
-    if (TL > 0 && a.offsets)
-        hipLaunchKernelGGL((gemm3_kernel<ENC, BN_, BM_, WN, WM, WS, XS, DW, TL>), grid,
-                           dim3(WN * WM * 64 + (DW ? 256 : 0)), 0, stream, a);
-    else
-        hipLaunchKernelGGL((gemm3_kernel<ENC, BN_, BM_, WN, WM, WS, XS, DW>), grid,
-                           dim3(WN * WM * 64 + (DW ? 256 : 0)), 0, stream, a);
-    return hipGetLastError();
-}
-
-template <int ENC>
-hipError_t launch_g3_variant(const GemmArgs &a, const LinearPlan &plan, hipStream_t stream)
-{
-    switch (plan.variant) {
-    case GEMM_G3_256x128: return launch_g3<ENC, 256, 128, 4, 2, 3, 3, true>(a, plan, stream);
-    default: return hipErrorInvalidValue;
+    if (plan.variant != GEMM_G3_256x128)
+        return hipErrorInvalidValue;
+    const int64_t nt = (a.n + G3::BN - 1) / G3::BN;
+    // grouped calls take up to 16 tail rows per expert
+    if (a.offsets) {
+        const dim3 grid((unsigned)(nt * plan.splits),
+                        (unsigned)token_tiles(a.rows, a.experts, true, G3::BM), 1);
+        hipLaunchKernelGGL((gemm3_kernel<ENC, 16>), grid, dim3(G3::THREADS), 0, stream, a);
+    } else {
+        const dim3 grid = dense_grid(nt * plan.splits * token_tiles(a.rows, 1, false, G3::BM));
+        hipLaunchKernelGGL((gemm3_kernel<ENC, 0>), grid, dim3(G3::THREADS), 0, stream, a);
     }
+    return hipGetLastError();
 }
 
 template <int MODE, int ENC, int BM, int WS, int XS, bool SPEC, int TL, int AUX>
@@ -955,7 +927,7 @@ hipError_t launch_g4_aux(const GemmArgs &a, const LinearPlan &plan, bool grouped
     const int64_t nt = (a.n + 127) / 128;
     const dim3 grid = grouped ? dim3((unsigned)(nt * plan.splits),
                                      (unsigned)token_tiles(a.rows, a.experts, true, BM), 1)
-                              : dense_grid(nt * plan.splits * ((a.rows + BM - 1) / BM));
+                              : dense_grid(nt * plan.splits * token_tiles(a.rows, 1, false, BM));
     const dim3 block(SPEC ? 768 : 512);
     if (TL > 0 && grouped)
         hipLaunchKernelGGL((gemm4_kernel<MODE, ENC, BM, WS, XS, SPEC, AUX, TL>), grid, block, 0,
@@ -1089,8 +1061,8 @@ hipError_t launch_gemm_fp8(int enc, const uint8_t *xq, const float *scale, const
     a.rotate = 0;
     if (plan.variant == GEMM_G3_256x256)
         return offsets ? hipErrorInvalidValue : launch_gemm256_fp8(enc, a, stream);
-    return enc == ENC_E4M3 ? launch_g3_variant<ENC_E4M3>(a, plan, stream)
-                           : launch_g3_variant<ENC_E5M2>(a, plan, stream);
+    return enc == ENC_E4M3 ? launch_g3<ENC_E4M3>(a, plan, stream)
+                           : launch_g3<ENC_E5M2>(a, plan, stream);
 }
 
 }  // namespace dps

@@ -28,25 +28,16 @@ struct GemmArgs {
 
 namespace {
 
-constexpr int BM = 128;  // default token tile of block_rows
-
-// Token range of this block: dense calls use grid.y as the token tile;
-// grouped calls walk the experts' tile counts.  Returns false if no work.
-// With tail > 0 (grouped calls) an expert's last tile also takes up to `tail`
-// rows beyond bm, so an expert of bm + 1 .. bm + tail rows is one tile, not
-// two: its weights are read once.  Such a range [m0, m1) spans more than bm
-// rows; the kernel treats rows m0 + bm .. m1 - 1 as its tail.  The tile
-// count per expert never grows, so the host's grid bound still holds.
+// Token range of a block of a grouped call: grid.y walks the experts' tile
+// counts.  Returns false if no work.  With tail > 0 an expert's last tile also
+// takes up to `tail` rows beyond bm, so an expert of bm + 1 .. bm + tail rows
+// is one tile, not two: its weights are read once.  Such a range [m0, m1) spans
+// more than bm rows; the kernel treats rows m0 + bm .. m1 - 1 as its tail.
+// The tile count per expert never grows, so the host's grid bound still holds.
 __device__ __forceinline__ bool block_rows(const GemmArgs &a, int64_t &e, int64_t &m0,
-                                           int64_t &m1, int bm = BM, int tail = 0)
+                                           int64_t &m1, int bm, int tail)
 {
     const int64_t t = blockIdx.y;
-    if (!a.offsets) {
-        e = 0;
-        m0 = t * bm;
-        m1 = m0 + bm < a.rows ? m0 + bm : a.rows;
-        return m0 < m1;
-    }
     int64_t cum = 0;
     int64_t prev = 0;
     for (int64_t ex = 0; ex < a.experts; ++ex) {
@@ -103,20 +94,13 @@ __device__ __forceinline__ void store_tile_out(const GemmArgs &a, int s, int64_t
 
 __device__ __attribute__((aligned(16))) const uint8_t g_zero16[16] = {0};
 
-#define DPS_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-
 // Cache policies of a direct-to-LDS load: plain, and nontemporal for weights
 // that are read once and do not stay cached (dps_gemm.hip, streams).
 enum { AUX_CACHED = 0, AUX_STREAM = 2 };
 
-__device__ __forceinline__ void dma16(const void *src, void *lds_wave_base)
-{
-    __builtin_amdgcn_global_load_lds(src, DPS_LDS(lds_wave_base), 16, 0, 0);
-}
-
-// The same, 16 bytes per lane from `src` into the wave's 1 KiB at LDS address
-// `lds` (lane l lands at lds + 16 l), as one asm statement without outputs.
-// The compiler takes the builtin for a flat access that may retire out of
+// 16 bytes per lane from `src` into the wave's 1 KiB at LDS address `lds` (lane
+// l lands at lds + 16 l), as one asm statement without outputs.  The compiler
+// takes the builtin for a flat access that may retire out of
 // order and then waits for lgkmcnt(0) before every use of an LDS read, where
 // the reads still in flight could stay so.  Completion is the caller's own
 // business (vmcnt, in issue order).
