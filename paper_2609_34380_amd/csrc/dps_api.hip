@@ -273,12 +273,14 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
         // not allow vector stores).  MI355X under sustained load (65 shapes of
         // twenty layers, both modes, weights in rotation), 128 / 256 tile in
         // full mode and the estimate's ratio: 16640 x 4096 at 257 tokens 66 /
-        // 93 us (1.34), O at 2048 78 / 82 (0.99), QKV at 1280 78 / 79 (0.98), at
-        // 2048 117 / 108 (0.90), at 2304 144 / 115 (0.73), down at 1280 1.44x
-        // (0.66).  The line stands at 1 and not lower because within a pass the
-        // 128-row tile also costs its neighbours: it draws more power (O at 2048
-        // tokens in fast mode on it 68 us, on big tiles 74, but gate+up 419
-        // against 393 and the pass 794 against 755).
+        // 93 us (1.34), O at 2048 75 / 83 (0.99), at 1920 71 / 79 (0.99), QKV at
+        // 1280 72 / 79 (0.98), gate+up at 300 112 / 116 (0.98), O at 3072 111 /
+        // 105 (0.90), QKV at 2048 121 / 106 (0.90), at 2304 144 / 115 (0.73), down
+        // at 1280 1.44x (0.66).  Big tiles are taken below 0.97: the shapes above
+        // it are 4-10% slower on them (fast mode 7-16%).  Not at much less: the
+        // 128-row tile draws more power, so a pass of sustained load loses a
+        // little where a call alone gains (hidden-4096 in fast mode at 2048
+        // tokens 743 us with O on big tiles, 763 so; full mode 856 and 850).
         // Decode-sized calls keep the 128-row tile (gate+up at 256 tokens 74 / 82).
         if (!grouped && rows > 256) {
             const int64_t cus = cu_count;
@@ -297,7 +299,7 @@ LinearPlan plan_linear(int mode, uint32_t flags, int64_t rows, int64_t n, int64_
                 const double partials = (double)s5 * (double)rows * (double)n / 8000.0;
                 const double big = rounds(t5 * s5) * (3.0 * (double)k / (double)s5 + 200.0) +
                                    (s5 == 1 ? 0.0 : (n % 4 ? 3.0 : 1.0) * partials);
-                if (s5 <= 4 && big < small)
+                if (s5 <= 4 && big < 0.97 * small)
                     p.variant = GEMM_G5_256x256;
             }
         }

@@ -238,7 +238,11 @@ def test_plan_info_names_the_kernel_of_each_shape_class(lib):
     (1920, 6144, 4096, 256, 1),    # the same big tiles at ...
     (2048, 6144, 4096, 256, 1),    # ... three whole rounds of small ones
     (1531, 4096, 4096, 256, 2),
-    (2048, 4096, 4096, 256, 2),
+    (1920, 4096, 4096, 128, 1),    # big tiles within a few percent: the small ones
+    (2048, 4096, 4096, 128, 1),
+    (1280, 6144, 4096, 128, 1),
+    (300, 28672, 4096, 128, 1),
+    (3072, 4096, 4096, 256, 1),
     (512, 28672, 4096, 256, 1),
     (500, 28672, 8192, 256, 1),    # below 512 tokens too
     (1280, 4096, 14336, 256, 3),
